@@ -99,11 +99,13 @@ typedef struct {
                                atomics; 2 = each thread owns grid cells of a tile (or, for
                                fp32 grids in d >= 2, of a sub-tile with one wavefront each)
                                and sums in registers in a fixed order (deterministic) */
-  int interp;               /* type-2 interpolation: 0 = default (d = 2: 2x2-bin tiles plus
-                               halo staged in LDS one grid pair at a time; d = 1, 3: as 2);
-                               1 = one thread per point reading its window through the
-                               caches; 2 = each bin's tile plus halo staged in LDS for a
-                               chunk of grid pairs, (point, window row, pair) items */
+  int interp;               /* type-2 interpolation: 0 = default (where many points share
+                               their cells, blocks of bins plus halo staged in LDS one grid
+                               pair at a time; else a group of lanes per point reading its
+                               window through the caches); 1 = one thread per point reading
+                               its window through the caches; 2 = each bin's tile plus halo
+                               staged in LDS for a chunk of grid pairs, (point, window row,
+                               pair) items */
   int step3;                /* step 3 of section 4.2 (rem:step3): 0 = precomputed tensor
                                A_k'k, stored once per distinct |n|^2 (default); 1 = direct
                                sum over the t nodes at every mode; 2 = the precomputed rows

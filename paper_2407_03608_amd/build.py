@@ -14,12 +14,14 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libgpnufft.so")
-# (source, object, extra flags): gp_mode.hip is built once per precision
+# (source, object, extra flags): gp_interp.hip and gp_mode.hip are built once per precision
 SOURCES = [
     ("gp_fft.hip", "gp_fft.o", []),
     ("gp_plan.hip", "gp_plan.o", []),
     ("gp_nufft.hip", "gp_nufft.o", []),
     ("gp_spread.hip", "gp_spread.o", []),
+    ("gp_interp.hip", "gp_interp64.o", ["-DGP_INTERP_FP64=1"]),
+    ("gp_interp.hip", "gp_interp32.o", ["-DGP_INTERP_FP64=0"]),
     ("gp_mode.hip", "gp_mode64.o", ["-DGP_MODE_FP64=1"]),
     ("gp_mode.hip", "gp_mode32.o", ["-DGP_MODE_FP64=0"]),
     ("gp_cg.hip", "gp_cg.o", []),

@@ -33,6 +33,10 @@ namespace gp {
 
 void mix_modes_fp64(Plan* P);
 void mix_modes_fp32(Plan* P);
+void interp_fp64(Plan* P, const Records& R, const double* xs, double* ys, int add_noise, int nsets,
+                 const void* grid, int64_t set_stride);
+void interp_fp32(Plan* P, const Records& R, const double* xs, double* ys, int add_noise, int nsets,
+                 const void* grid, int64_t set_stride);
 static void mix_modes(Plan* P) {
   if (P->precision == GP_FP64)
     mix_modes_fp64(P);
@@ -553,205 +557,6 @@ __global__ __launch_bounds__(kThreads) void interp_kernel(
   }
 }
 
-// ------------------------------------------------- interp (2x2 super-tile) ----
-// d = 2, 3.  One workgroup per chunk of the points of a 2x2(x1) block of bins: the
-// block's cells plus the (w-1) halo are staged in LDS for one grid pair at a
-// time (halo overhead (2t+w-1)^2/(2t)^2 instead of (t+w-1)^2/t^2 per bin), the
-// points' rows are staged once, and each thread keeps its items' partial sums
-// over all pairs in registers.  Items are (row group, point), row group
-// fastest; the RG lanes of a point combine by xor shuffles at the end, so the
-// order of every sum is fixed.  The next pair's tile is loaded into registers
-// while the current pair is computed (the kernel is otherwise latency-bound:
-// 1.71 -> 0.88 ms at d=2 N=1e6 fp64 on the 8192^2 grid).
-// Points staged per batch: 128 for fp32 grids (in 3-D the 2x2x1 block of
-// 20 x 20 x 12 cells at w = 5 and the rows then take 49 KB, three workgroups
-// per CU: d=3 N=1e7 3.19 -> 2.71 ms against 320 points per batch at 80 KB,
-// although the block is staged more often); 64 for fp64 grids, whose rows of
-// 38 doubles per point would otherwise hold two workgroups per CU (d=2 N=1e6:
-// three, with the block staged about twice as often, 0.79 -> 0.70 ms).
-template <int D, typename T>
-constexpr int kPB2 = sizeof(T) == 8 ? 64 : 128;
-
-// tile cells per thread kept in flight by the pipelined variant (a d=3 block
-// of 2x2x1 bins of 8^3 cells with w = 5 has 20 x 20 x 12 = 4800 cells)
-template <int D>
-constexpr int kTE = D > 2 ? 20 : 8;
-
-// W > 0: the window width as a compile-time constant (inner loops unrolled);
-// W = 0 reads it from the arguments.
-template <typename T, bool PIPE, int D, int W>
-__global__ __launch_bounds__(kThreads) void interp_super_kernel(
-    NuArgs a, const typename V2<T>::type* __restrict__ grid, const int* __restrict__ cell,
-    const T* __restrict__ pw, int rs, const int* __restrict__ bin_start,
-    const int4* __restrict__ work, const double* __restrict__ x, double* __restrict__ y,
-    int64_t nwork, int grp) {
-  using V = typename V2<T>::type;
-  constexpr int PB = kPB2<D, T>;
-  constexpr int NI = (PB * kRG + kThreads - 1) / kThreads;  // items per thread
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int w = W > 0 ? W : a.w;
-  // blocks of 2 x 2 (x 1) bins: the first two dimensions doubled
-  const int st0 = 2 * a.tile[0], st1 = 2 * a.tile[1], st2 = D > 2 ? a.tile[2] : 1;
-  const int pc0 = st0 + w - 1, pc1 = st1 + w - 1, pc2 = D > 2 ? st2 + w - 1 : 1;
-  const int ps0 = pc0 | 1;  // odd row stride: the RG lanes of a point hit different banks
-  const int ls = lds_stride(rs);
-  V* tile = reinterpret_cast<V*>(smem);                              // [pc2][pc1][ps0]
-  T* s_rec = reinterpret_cast<T*>(tile + (size_t)ps0 * pc1 * pc2);   // [PB][ls]
-  int* s_cell = reinterpret_cast<int*>(s_rec + PB * ls);           // [PB][D]
-  int* s_idx = s_cell + D * PB;                                     // [PB] sorted index
-
-  // block -> work item: groups of grp consecutive items per XCD (blocks go to
-  // the XCDs round-robin); the grid is padded to a multiple of 8 grp
-  int64_t item = blockIdx.x;
-  if (grp > 0) {
-    const int64_t xx = item % 8, k = item / 8;
-    item = ((k / grp) * 8 + xx) * grp + k % grp;
-    if (item >= nwork) return;
-  }
-  const int4 wk = work[item];
-  const int nsb0 = (a.nbins[0] + 1) / 2, nsb1 = (a.nbins[1] + 1) / 2;
-  const int sx = wk.x % nsb0, sy = (wk.x / nsb0) % nsb1, sz = D > 2 ? wk.x / (nsb0 * nsb1) : 0;
-  const int t00 = sx * st0, t01 = sy * st1, t02 = sz * st2;
-  const int bx0 = 2 * sx, bx1 = min(2 * sx + 1, a.nbins[0] - 1);
-  int r_lo[2] = {0, 0}, r_len0 = 0;
-  for (int q = 0; q < 2; ++q) {
-    const int by = 2 * sy + q;
-    if (by >= a.nbins[1]) break;
-    const int64_t rowbin = ((int64_t)sz * a.nbins[1] + by) * a.nbins[0];
-    r_lo[q] = bin_start[rowbin + bx0];
-    if (q == 0) r_len0 = bin_start[rowbin + bx1 + 1] - r_lo[0];
-  }
-  const int cellsw = D > 2 ? w * w : w;  // window rows per point
-  const int RG = cellsw >= kRG ? kRG : (cellsw >= 2 ? 2 : 1);  // power of two; kThreads % RG == 0
-  const int wko = D * w;
-  for (int pos = wk.y; pos < wk.z; pos += PB) {
-    const int np = min(PB, wk.z - pos);
-    __syncthreads();
-    for (int e = threadIdx.x; e < np; e += kThreads) {
-      const int q = pos + e;
-      const int idx = q < r_len0 ? r_lo[0] + q : r_lo[1] + (q - r_len0);
-      s_idx[e] = idx;
-      s_cell[D * e] = cell[idx] - t00;
-      s_cell[D * e + 1] = cell[a.n + idx] - t01;
-      if (D > 2) s_cell[D * e + 2] = cell[2 * a.n + idx] - t02;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < np * rs; e += kThreads) {
-      const int p = e / rs, c = e - p * rs;
-      s_rec[p * ls + c] = pw[(int64_t)s_idx[p] * rs + c];
-    }
-    double part[NI];
-#pragma unroll
-    for (int k = 0; k < NI; ++k) part[k] = 0.0;
-    const int nitems = np * RG;
-    const int ucells = pc0 * pc1 * pc2;
-    // PIPE: the next pair's tile is loaded into registers while this pair is
-    // computed, and stored to LDS after the barrier (ucells <= kTE kThreads)
-    V nxt[PIPE ? kTE<D> : 1];
-    auto load_tile = [&](int g) {
-#pragma unroll
-      for (int j = 0; j < (PIPE ? kTE<D> : 1); ++j) {
-        const int e = threadIdx.x + j * kThreads;
-        V v = V{T(0), T(0)};
-        if (e < ucells) {
-          const int l12 = e / pc0, l0 = e - l12 * pc0;
-          const int l1 = D > 2 ? l12 % pc1 : l12, l2 = D > 2 ? l12 / pc1 : 0;
-          const int c0 = t00 + l0, c1 = t01 + l1, c2 = t02 + l2;
-          if (c0 < a.na[0] && c1 < a.na[1] && (D < 3 || c2 < a.na[2]))
-            v = grid[(int64_t)g * a.pair_stride + a.grid_off + (int64_t)c0 * a.gstride[0] +
-                     (int64_t)c1 * a.gstride[1] + (D > 2 ? (int64_t)c2 * a.gstride[2] : 0)];
-        }
-        nxt[j] = v;
-      }
-    };
-    if (PIPE) load_tile(0);
-    for (int g = 0; g < a.npair; ++g) {
-      __syncthreads();  // records staged / previous pair's tile no longer read
-      if (PIPE) {
-#pragma unroll
-        for (int j = 0; j < (PIPE ? kTE<D> : 1); ++j) {
-          const int e = threadIdx.x + j * kThreads;
-          if (e < ucells) {
-            const int l12 = e / pc0, l0 = e - l12 * pc0;
-            tile[l12 * ps0 + l0] = nxt[j];
-          }
-        }
-        if (g + 1 < a.npair) load_tile(g + 1);
-      } else {
-        // cell (l0, l1, l2) of the thread's e, stepped by kThreads = s12 rows + s0 cells
-        const int s12 = kThreads / pc0, s0 = kThreads - s12 * pc0;
-        int l0 = threadIdx.x % pc0, l1 = threadIdx.x / pc0, l2 = 0;
-        while (l1 >= pc1) { l1 -= pc1; ++l2; }
-        for (int e = threadIdx.x; e < ucells; e += kThreads) {
-          const int c0 = t00 + l0, c1 = t01 + l1, c2 = t02 + l2;
-          V v = V{T(0), T(0)};
-          if (c0 < a.na[0] && c1 < a.na[1] && (D < 3 || c2 < a.na[2]))
-            v = grid[(int64_t)g * a.pair_stride + a.grid_off + (int64_t)c0 * a.gstride[0] +
-                     (int64_t)c1 * a.gstride[1] + (D > 2 ? (int64_t)c2 * a.gstride[2] : 0)];
-          tile[(l2 * pc1 + l1) * ps0 + l0] = v;
-          l0 += s0;
-          l1 += s12;
-          if (l0 >= pc0) { l0 -= pc0; ++l1; }
-          while (l1 >= pc1) { l1 -= pc1; ++l2; }
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < NI; ++k) {
-        const int it = threadIdx.x + k * kThreads;
-        if (it < nitems) {
-          const int rg = it % RG, p = it / RG;
-          const T* pr = s_rec + p * ls;
-          const int o0 = s_cell[D * p], o1 = s_cell[D * p + 1], o2 = D > 2 ? s_cell[D * p + 2] : 0;
-          // beta_2g, beta_2g+1 over this item's window rows, then weighted in fp64
-          T sx = 0, sy = 0;
-          // window row (q1, q2) of row index q2 w + q1, stepped by RG < w
-          int q1 = D > 2 ? (rg < w ? rg : rg - w) : rg, q2 = D > 2 && rg >= w ? 1 : 0;
-          for (int row = rg; row < cellsw; row += RG) {
-            const V* tr = tile + ((o2 + q2) * pc1 + (o1 + q1)) * ps0 + o0;
-            T rx = 0, ry = 0;
-            if constexpr (W > 0) {
-#pragma unroll
-              for (int q0 = 0; q0 < W; ++q0) {
-                const T ps = pr[q0];
-                const V gv = tr[q0];
-                rx += ps * gv.x;
-                ry += ps * gv.y;
-              }
-            } else {
-              for (int q0 = 0; q0 < w; ++q0) {
-                const T ps = pr[q0];
-                const V gv = tr[q0];
-                rx += ps * gv.x;
-                ry += ps * gv.y;
-              }
-            }
-            const T wv = D > 2 ? pr[w + q1] * pr[2 * w + q2] : pr[w + row];
-            sx += wv * rx;
-            sy += wv * ry;
-            q1 += RG;
-            if (D > 2) {
-              while (q1 >= w) { q1 -= w; ++q2; }
-            }
-          }
-          part[k] += (double)pr[wko + 2 * g] * (double)sx + (double)pr[wko + 2 * g + 1] * (double)sy;
-        }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      const int it = threadIdx.x + k * kThreads;  // a lane group is all in or all out
-      double v = part[k];
-      if (RG >= 2) v += __shfl_xor(v, 1);
-      if (RG >= 4) v += __shfl_xor(v, 2);
-      if (it < nitems && it % RG == 0) {
-        const int i = s_idx[it / RG];
-        y[i] = (a.add_noise ? a.eta2 * x[i] : 0.0) + v;
-      }
-    }
-  }
-}
-
 __global__ void gather_kernel(int64_t n, const int* __restrict__ perm, const double* __restrict__ u,
                               double* __restrict__ s) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -875,9 +680,6 @@ void allow_big_lds(K kernel) {
   GP_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmemBig));
   done.push_back(f);
 }
-// The 2x2(x1)-bin interpolation takes up to 80 KB: two workgroups per CU.
-constexpr size_t kSmemSuper = 80 * 1024;
-
 template <typename T, int D>
 void launch_interp(Plan* P, const Records& R, const double* xs, double* ys, int add_noise) {
   PhaseScope ps(P, PH_INTERP);
@@ -934,50 +736,24 @@ void launch_interp_gather(Plan* P, const Records& R, const double* xs, double* y
   GP_CHECK_LAUNCH();
 }
 
+// The points of R for nsets consecutive vectors (and the grid sets from the
+// current one on).
 template <typename T>
-size_t interp_super_smem(const Plan* P, int rs) {
-  const size_t pc0 = (size_t)(2 * P->tile[0] + P->w - 1), pc1 = (size_t)(2 * P->tile[1] + P->w - 1);
-  const size_t pc2 = P->d > 2 ? (size_t)(P->tile[2] + P->w - 1) : 1;
-  return (pc0 | 1) * pc1 * pc2 * sizeof(typename V2<T>::type) +
-         (size_t)(P->d > 2 ? kPB2<3, T> : kPB2<2, T>) * (lds_stride(rs) * sizeof(T) + (P->d + 1) * sizeof(int)) + 16;
-}
-
-template <typename T>
-void launch_interp_super(Plan* P, const Records& R, const double* xs, double* ys, int add_noise) {
-  PhaseScope ps(P, PH_INTERP);
-  NuArgs a = nu_args(P, R);
-  a.add_noise = add_noise;
-  if (R.n_in_work2 == 0) return;
-  const int ucells = (2 * P->tile[0] + P->w - 1) * (2 * P->tile[1] + P->w - 1) *
-                     (P->d > 2 ? P->tile[2] + P->w - 1 : 1);
-  // software-pipelined tile loads when a pair's tile fits kTE cells per thread
-  const bool pipe = ucells <= (P->d > 2 ? kTE<3> : kTE<2>) * kThreads;
-  // compile-time window widths of the common plans (fp32 at tol 1e-4: 5 in
-  // 3-D, 7 in 2-D at the automatic oversampling; fp64 at 1e-8 in 2-D: 12)
-  auto pick = [&](auto d2, auto d3) { return P->d == 2 ? d2 : d3; };
-  auto kern = pipe ? (P->w == 5    ? pick(interp_super_kernel<T, true, 2, 5>, interp_super_kernel<T, true, 3, 5>)
-                      : P->w == 7  ? pick(interp_super_kernel<T, true, 2, 7>, interp_super_kernel<T, true, 3, 7>)
-                      : P->w == 12 ? pick(interp_super_kernel<T, true, 2, 12>, interp_super_kernel<T, true, 3, 12>)
-                                   : pick(interp_super_kernel<T, true, 2, 0>, interp_super_kernel<T, true, 3, 0>))
-                   : pick(interp_super_kernel<T, false, 2, 0>, interp_super_kernel<T, false, 3, 0>);
-  if (interp_super_smem<T>(P, R.rs) > kSmemCap) allow_big_lds(kern);
-  // work items (2x2 bin blocks in raster order) are dealt to the 8 XCDs in
-  // groups of 16 consecutive ones, so neighbouring blocks, whose halos
-  // overlap, read them through one L2 (d=3 N=1e7: 3.50 -> 3.20 ms)
-  constexpr int grp = 16;
-  const int64_t nw = R.n_in_work2;
-  const int64_t nblk = grp > 0 ? (nw + 8 * grp - 1) / (8 * grp) * (8 * grp) : nw;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(kThreads),
-                     interp_super_smem<T>(P, R.rs), P->stream, a,
-                     cur_gridA<typename V2<T>::type>(P), R.cell.as<int>(), R.pw.as<T>(), R.rs,
-                     R.bin_start.as<int>(), R.in_work2.as<int4>(), xs, ys, nw, grp);
-  GP_CHECK_LAUNCH();
-}
-
-template <typename T>
-void interp_dispatch(Plan* P, const Records& R, const double* xs, double* ys, int add_noise) {
-  if (P->interp_mode == 0 && P->d >= 2 && interp_super_smem<T>(P, R.rs) <= kSmemSuper) {
-    launch_interp_super<T>(P, R, xs, ys, add_noise);
+void interp_dispatch(Plan* P, const Records& R, const double* xs, double* ys, int add_noise,
+                     int nsets = 1) {
+  using V = typename V2<T>::type;
+  if (P->interp_mode == 0) {
+    const int64_t set = (int64_t)P->npair * P->grid_elems[P->fourstep ? 3 : 0];
+    (sizeof(T) == 8 ? interp_fp64 : interp_fp32)(P, R, xs, ys, add_noise, nsets, cur_interp_grid<V>(P), set);
+    return;
+  }
+  if (nsets > 1) {
+    const int cur = P->gv.cur;
+    for (int j = 0; j < nsets; ++j) {
+      P->gv.cur = cur + j;
+      interp_dispatch<T>(P, R, xs + j * R.n, ys + j * R.n, add_noise);
+    }
+    P->gv.cur = cur;
     return;
   }
   if (P->interp_mode == 1) {  // cache-gather variant
@@ -1251,11 +1027,9 @@ void matvec_multi_sorted(Plan* P, int m, const double* xs, double* ys, int add_n
     fft_all(P, -1);
     mix_modes(P);
     fft_all(P, +1);
-    for (int j = 0; j < m; ++j) {
-      P->gv.cur = j;
-      if (P->precision == GP_FP64) interp_dispatch<double>(P, P->rec, xs + j * n, ys + j * n, add_noise);
-      else interp_dispatch<float>(P, P->rec, xs + j * n, ys + j * n, add_noise);
-    }
+    P->gv.cur = 0;
+    if (P->precision == GP_FP64) interp_dispatch<double>(P, P->rec, xs, ys, add_noise, m);
+    else interp_dispatch<float>(P, P->rec, xs, ys, add_noise, m);
   } catch (...) {
     P->gv = own;
     throw;

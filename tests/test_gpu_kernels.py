@@ -1,0 +1,62 @@
+"""GPU: kernel variants and dispatch rules at the edges of their tiles.
+
+Each test compares a kernel that a rule selects with the general path of the
+same library (itself checked against the oracle in test_gpu_parity.py) or with
+the oracle, at sizes where tiles, remainders and window widths can go wrong.
+"""
+import numpy as np
+import pytest
+
+from paper_2407_03608_amd import inputs
+from tests.gpu_common import cuda, host, max_rel, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gp():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2407_03608_amd import gp as g
+    g.load()
+    return g
+
+
+def _matvec(gp, prob, a, **kw):
+    P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, **kw)
+    return host(P.matvec(cuda(a), add_noise=True)), P.info()
+
+
+# Sums of w^d N_sigma products in another order: below 4e-14 (fp64, 343 terms of
+# rounding 1.1e-16) and 2e-5 (fp32, 6e-8) of the largest value, with a factor for
+# the cancellation among the weights w_k.
+ORDER_FP64 = 2e-13
+ORDER_FP32 = 3e-5
+
+
+@pytest.mark.parametrize("d,n,M,tol,prec", [
+    # window widths of fp64 and fp32 plans, points dense enough for staged blocks
+    (2, 1500, 24, 1e-2, 0), (2, 1500, 24, 1e-5, 0), (2, 1700, 30, 1e-8, 0), (2, 1300, 40, 1e-11, 0),
+    (2, 1500, 24, 1e-2, 1), (2, 2100, 40, 1e-4, 1), (2, 1500, 33, 1e-6, 1),
+    # the same grids with few points: a group of lanes per point
+    (2, 1, 24, 1e-8, 0), (2, 37, 60, 1e-8, 0), (2, 37, 60, 1e-4, 1),
+    (3, 4000, 8, 1e-2, 0), (3, 6000, 10, 1e-6, 0), (3, 3000, 10, 1e-9, 0), (3, 25, 12, 1e-8, 0),
+    (3, 4000, 8, 1e-2, 1), (3, 6000, 12, 1e-4, 1), (3, 9000, 9, 1e-6, 1), (3, 25, 12, 1e-4, 1),
+    (1, 1, 20, 1e-8, 0), (1, 300, 150, 1e-3, 1), (1, 777, 9000, 1e-8, 0), (1, 5000, 60, 1e-12, 0),
+])
+def test_interp_default_matches_per_bin(gp, d, n, M, tol, prec):
+    """The default interpolation (staged blocks or lane groups, by density)
+    against the per-bin kernel, on clustered and uniform points."""
+    for clustered in (False, True):
+        prob = inputs.random_small(d, n, seed=7 * d + n, nu=1.5, lmin=0.1, lmax=0.25)
+        if clustered:  # a third of the points in one cell-sized cluster, corners included
+            rng = np.random.default_rng(n)
+            k = max(1, n // 3)
+            prob.x[:k] = 0.5 + 1e-3 * rng.standard_normal((k, d))
+            prob.x[0], prob.x[-1] = 0.0, 1.0
+        a = np.random.default_rng(1).standard_normal(n)
+        got, info = _matvec(gp, prob, a, tol=tol, precision=prec, M=M)
+        ref, _ = _matvec(gp, prob, a, tol=tol, precision=prec, M=M, interp=2)
+        e = max_rel(got, ref)
+        say(f"interp d={d} n={n} w={info['w']} na={info['na']} prec={prec} clustered={clustered}: {e:.2e}")
+        assert e <= (ORDER_FP32 if prec else ORDER_FP64), e
