@@ -213,20 +213,29 @@ struct KParams {
   int64_t in_cs1, in_es1, out_cs1, out_es1;
   int in_cps, in_ips, out_cps, out_ips;  // log2 of the interleave factors (0 or 1)
   int n_in, in_start, n_out, out_start, sign;
-  int64_t L4, tw4_mod;
-  int tw4_at_load;
+  // four-step passes (1-D): rows per grid, transform length, kept modes -M..M
+  int tw4_mod, nf4, band;
 };
+
+// Element access of a pass: plain 64-bit addresses, buffer resources, or the
+// contiguous rows of a 1-D four-step transform (buffer resources, with its
+// twiddles and the band of kept modes).
+enum { kPlain = 0, kBuf = 1, kFour = 2 };
+// four-step row k2, element k1 is mode k = k2 + L2 k1 (mod nf) of -M..M
+__device__ __forceinline__ bool four_kept(int k, const KParams& p) {
+  return k <= p.band || k >= p.nf4 - p.band;
+}
 
 // Stage with sub-transform length Ls and radix R on the registers v:
 // butterfly j = jt + TPT u (u < EPT/R), k = j mod Ls, inputs v[u R + m] =
 // X[j + m L/R], twiddle exp(s 2 pi i k m / (Ls R)) (one table load, powers by
 // recurrence), outputs Y[(j - k) R + k + q Ls].  Then either exchange through
 // LDS into the next stage's inputs or, on the last stage, store.
-template <typename T, typename V, int L, int EPT, int Ls, bool BUF>
+template <typename T, typename V, int L, int EPT, int Ls, int MODE>
 __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
                                        const V* __restrict__ tw, int s, bool act, V* dst,
                                        int64_t dstride, const KParams& p, const V* tw4,
-                                       int64_t row4, __amdgpu_buffer_rsrc_t orsrc, int odl) {
+                                       int row4, __amdgpu_buffer_rsrc_t orsrc, int odl) {
   constexpr int TPT = L / EPT;
   constexpr int R = next_radix(L / Ls, EPT);
   static_assert(R > 0, "unsupported FFT length");
@@ -278,12 +287,30 @@ __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
       }
       __syncthreads();
     }
-    stages<T, V, L, EPT, Ls * R, BUF>(v, buf, jt, tw, s, act, dst, dstride, p, tw4, row4, orsrc,
+    stages<T, V, L, EPT, Ls * R, MODE>(v, buf, jt, tw, s, act, dst, dstride, p, tw4, row4, orsrc,
                                       odl);
   } else {
     // last stage: k = j, outputs at j + q L/R
     if (!act) return;
-    if constexpr (BUF) {
+    if constexpr (MODE == kFour) {
+      // inverse: the four-step twiddle; forward: only the modes -M..M are kept
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const int pos = jt + TPT * u + q * (L / R);
+          V val = v[u * R + q];
+          if (s > 0) {
+            V wv = tw4[pos * row4];
+            wv.y = -wv.y;
+            val = cmul(val, wv);
+          }
+          const bool ok = s > 0 || four_kept(pos * p.tw4_mod + row4, p);
+          buf_store(val, orsrc, ok ? (unsigned)(odl + pos) * (unsigned)sizeof(V) : kBufOut);
+        }
+      return;
+    }
+    if constexpr (MODE == kBuf) {
       const int pm = (1 << p.out_ips) - 1;
       const int oes = (int)dstride, oes1 = (int)p.out_es1;
       const int i0 = jt - p.out_start;
@@ -307,13 +334,7 @@ __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
         int i = pos - p.out_start;
         if (i < 0) i += L;
         if (i < p.n_out) {
-          V val = v[u * R + q];
-          if (tw4 != nullptr && !p.tw4_at_load) {
-            V wv = tw4[((int64_t)pos * row4) % p.L4];
-            if (s > 0) wv.y = -wv.y;
-            val = cmul(val, wv);
-          }
-          dst[elem_off(i, p.out_ips, dstride, p.out_es1)] = val;
+          dst[elem_off(i, p.out_ips, dstride, p.out_es1)] = v[u * R + q];
         }
       }
     }
@@ -335,7 +356,7 @@ constexpr int fft_waves(int L, int EPT, int B, int tb) {
   return m < 1 ? 1 : (m > 8 ? 8 : m);
 }
 
-template <typename T, int L, int EPT, int B, bool BUF, int S>
+template <typename T, int L, int EPT, int B, int MODE, int S>
 __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) void fft_pass_kernel(
     const typename V2<T>::type* __restrict__ in, typename V2<T>::type* __restrict__ out,
     const typename V2<T>::type* __restrict__ tw, const typename V2<T>::type* __restrict__ tw4,
@@ -366,13 +387,37 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
   const int64_t o = act ? t / p.inner : 0, c = act ? t - o * p.inner : 0;
   const V* src = in + o * p.in_os + (c >> p.in_cps) * p.in_cs + (c & ((1 << p.in_cps) - 1)) * p.in_cs1;
   V* dst = out + o * p.out_os + (c >> p.out_cps) * p.out_cs + (c & ((1 << p.out_cps) - 1)) * p.out_cs1;
-  const int64_t row4 = tw4 != nullptr ? o % p.tw4_mod : 0;
+  const int row4 = MODE == kFour ? (int)(o % p.tw4_mod) : 0;
   constexpr int R1 = next_radix(L, EPT);
   constexpr int NB1 = EPT / R1;
   V v[EPT];
   __amdgpu_buffer_rsrc_t orsrc = buf_rsrc(out);
   int odl = 0;
-  if constexpr (BUF) {
+  if constexpr (MODE == kFour) {
+    // bound by latency (the grids stay in the caches): 32-bit table indices (k2 l1
+    // < nf needs no reduction), and the band test on load and store instead of a
+    // pass that clears the other modes
+    // row t of the batch: L contiguous elements (inner = 1)
+    const int64_t t0 = bid * B;
+    const __amdgpu_buffer_rsrc_t irsrc = buf_rsrc(in + t0 * L);
+    orsrc = buf_rsrc(out + t0 * L);
+    odl = b * L;
+#pragma unroll
+    for (int u = 0; u < NB1; ++u)
+#pragma unroll
+      for (int m = 0; m < R1; ++m) {
+        const int pos = jt + TPT * u + m * (L / R1);
+        const bool ok = act && (S < 0 || four_kept(pos * p.tw4_mod + row4, p));
+        v[u * R1 + m] = buf_load(irsrc, ok ? (unsigned)(odl + pos) * (unsigned)sizeof(V) : kBufOut, (V*)nullptr);
+      }
+    if (S < 0) {
+#pragma unroll
+      for (int u = 0; u < NB1; ++u)
+#pragma unroll
+        for (int m = 0; m < R1; ++m)
+          v[u * R1 + m] = cmul(v[u * R1 + m], tw4[(jt + TPT * u + m * (L / R1)) * row4]);
+    }
+  } else if constexpr (MODE == kBuf) {
     // line starts are non-decreasing in the transform index (checked on the
     // host), so the workgroup's first line is its lowest
     const int64_t t0 = bid * B;
@@ -406,18 +451,11 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
       int i = pos - p.in_start;
       if (i < 0) i += L;
       V val = V{T(0), T(0)};
-      if (act && i < p.n_in) {
-        val = src[elem_off(i, p.in_ips, p.in_es, p.in_es1)];
-        if (tw4 != nullptr && p.tw4_at_load) {
-          V wv = tw4[((int64_t)pos * row4) % p.L4];
-          if (S > 0) wv.y = -wv.y;
-          val = cmul(val, wv);
-        }
-      }
+      if (act && i < p.n_in) val = src[elem_off(i, p.in_ips, p.in_es, p.in_es1)];
       v[u * R1 + m] = val;
     }
   }
-  stages<T, V, L, EPT, 1, BUF>(v, buf + b * LP, jt, tw, S, act, dst, p.out_es, p, tw4, row4,
+  stages<T, V, L, EPT, 1, MODE>(v, buf + b * LP, jt, tw, S, act, dst, p.out_es, p, tw4, row4,
                                orsrc, odl);
 }
 
@@ -432,11 +470,10 @@ constexpr int batch_for(int L, int elem_bytes) {
 }
 
 // Whether workgroups of B consecutive transforms can use buffer addressing:
-// no four-step twiddles, non-negative strides, line starts non-decreasing in
+// non-negative strides, line starts non-decreasing in
 // the transform index (so a workgroup's first line is its lowest), and every
 // byte offset from a workgroup's first line below kBufRange.
 bool buf_fits(const KParams& p, const FftPass& q, int B, int64_t vb) {
-  if (q.tw4 != nullptr) return false;
   auto side = [&](int64_t os, int64_t cs, int64_t cs1, int cps, int64_t es, int64_t es1, int ips,
                   int n) {
     if (os < 0 || cs < 0 || cs1 < 0 || es < 0 || es1 < 0) return false;
@@ -459,27 +496,38 @@ bool buf_fits(const KParams& p, const FftPass& q, int B, int64_t vb) {
 }
 
 template <typename T, int L, int EPT, int B>
-void launch_kernel(bool buf, int64_t nblk, const KParams& p, const void* in, void* out,
-                   const void* tw, const void* tw4, hipStream_t s) {
+void launch_kernel(const FftPass& q, const KParams& p, const void* in, void* out, const void* tw,
+                   hipStream_t s) {
   using V = typename V2<T>::type;
+  const int64_t nblk = (p.ntrans + B - 1) / B;
   if (nblk <= 0) return;
   const dim3 g((unsigned)nblk), t(B * (L / EPT));
-  const V *i = static_cast<const V*>(in), *w = static_cast<const V*>(tw), *w4 = static_cast<const V*>(tw4);
+  const V *i = static_cast<const V*>(in), *w = static_cast<const V*>(tw), *w4 = static_cast<const V*>(q.tw4);
   V* o = static_cast<V*>(out);
-  if (buf && p.sign < 0)
-    hipLaunchKernelGGL((fft_pass_kernel<T, L, EPT, B, true, -1>), g, t, 0, s, i, o, w, w4, p);
-  else if (buf)
-    hipLaunchKernelGGL((fft_pass_kernel<T, L, EPT, B, true, 1>), g, t, 0, s, i, o, w, w4, p);
-  else if (p.sign < 0)
-    hipLaunchKernelGGL((fft_pass_kernel<T, L, EPT, B, false, -1>), g, t, 0, s, i, o, w, w4, p);
-  else
-    hipLaunchKernelGGL((fft_pass_kernel<T, L, EPT, B, false, 1>), g, t, 0, s, i, o, w, w4, p);
+#define GP_FFT_GO(MODE)                                                                              \
+  do {                                                                                               \
+    if (p.sign < 0)                                                                                  \
+      hipLaunchKernelGGL((fft_pass_kernel<T, L, EPT, B, MODE, -1>), g, t, 0, s, i, o, w, w4, p);     \
+    else                                                                                             \
+      hipLaunchKernelGGL((fft_pass_kernel<T, L, EPT, B, MODE, 1>), g, t, 0, s, i, o, w, w4, p);      \
+  } while (0)
+  if (q.tw4 != nullptr) {
+    if (q.inner != 1 || q.in_os != L || q.out_os != L || q.n_in != L || q.n_out != L)
+      throw Error{GP_EINVAL, "fft_pass: a four-step pass takes whole contiguous rows"};
+    GP_FFT_GO(kFour);
+  } else if (buf_fits(p, q, B, (int64_t)sizeof(V))) {
+    GP_FFT_GO(kBuf);
+  } else {
+    GP_FFT_GO(kPlain);
+  }
+#undef GP_FFT_GO
   GP_CHECK_LAUNCH();
 }
 
+constexpr int64_t kFewBlocks = 512;
+
 template <typename T, int L>
 void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hipStream_t s) {
-  using V = typename V2<T>::type;
   constexpr int EPT = ept_for(L);
   constexpr int B = batch_for(L, (int)sizeof(T));
   KParams p;
@@ -504,9 +552,23 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
   p.n_out = q.n_out;
   p.out_start = ((q.out_start % L) + L) % L;
   p.sign = q.sign;
-  p.L4 = q.L4 > 0 ? q.L4 : 1;
-  p.tw4_mod = q.L4 > 0 ? (q.L4 / L) : 1;
-  p.tw4_at_load = q.tw4_at_load;
+  p.tw4_mod = q.L4 > 0 ? (int)(q.L4 / L) : 1;
+  p.nf4 = (int)q.L4;
+  p.band = (int)q.band;
+  // Few transforms (1-D four-step passes, small grids): half the elements per
+  // thread and workgroups of one wave, so that the batch reaches every CU.  The
+  // line is two workgroups per CU of the other form: below it those leave CUs
+  // idle (d=1 N=2000, 12 grids of 192 x 256: 72 and 96 workgroups; with the
+  // four-step rows' changes 0.015 / 0.022 / 0.026 / 0.018 -> 0.006 / 0.007 /
+  // 0.007 / 0.007 ms per pass).
+  if constexpr (L >= 64 && L <= 1024) {
+    if ((p.ntrans + B - 1) / B < kFewBlocks) {
+      constexpr int ES = L % 3 == 0 ? 12 : 16;
+      constexpr int BS = 64 / (L / ES) > 1 ? 64 / (L / ES) : 1;
+      launch_kernel<T, L, ES, BS>(q, p, in, out, tw, s);
+      return;
+    }
+  }
   // 8192-point passes.  Rows (and fp64 columns): 16 elements per thread, 512
   // threads, half the VGPRs of 32 per thread, so twice the waves per CU to
   // cover the memory latency.  fp32 columns: four adjacent columns per
@@ -514,15 +576,14 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
   // contiguous bytes; the column passes are bound by cache-line requests per
   // byte, and this wins (0.81 -> 0.72 ms) even though the 128-VGPR budget of a
   // 1024-thread workgroup spills a few registers.
-  const int64_t vb = (int64_t)sizeof(V);
   if constexpr (L == 8192) {
     if constexpr (sizeof(T) == 4) {
       if (q.inner > 1) {
-        launch_kernel<T, L, 32, 4>(buf_fits(p, q, 4, vb), (p.ntrans + 3) / 4, p, in, out, tw, q.tw4, s);
+        launch_kernel<T, L, 32, 4>(q, p, in, out, tw, s);
         return;
       }
     }
-    launch_kernel<T, L, 16, 1>(buf_fits(p, q, 1, vb), p.ntrans, p, in, out, tw, q.tw4, s);
+    launch_kernel<T, L, 16, 1>(q, p, in, out, tw, s);
   } else {
     // Long strided (column) fp32 transforms: two columns per workgroup, so
     // pairs of adjacent lanes read adjacent elements of one cache line.  fp64
@@ -530,11 +591,11 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
     // the forward column pass at d=2 N=1e6 with contiguous output).
     if constexpr (B == 1 && L >= 6144) {
       if (q.inner > 1 && sizeof(T) == 4) {
-        launch_kernel<T, L, EPT, 2>(buf_fits(p, q, 2, vb), (p.ntrans + 1) / 2, p, in, out, tw, q.tw4, s);
+        launch_kernel<T, L, EPT, 2>(q, p, in, out, tw, s);
         return;
       }
     }
-    launch_kernel<T, L, EPT, B>(buf_fits(p, q, B, vb), (p.ntrans + B - 1) / B, p, in, out, tw, q.tw4, s);
+    launch_kernel<T, L, EPT, B>(q, p, in, out, tw, s);
   }
 }
 

@@ -55,8 +55,11 @@ void pinned_scalars_put(double* h);
 // i = (pos - in_start) mod L and i < n_in (other positions are zero); the
 // output keeps positions out_start .. out_start + n_out - 1 (mod L) at
 // out[o*out_os + i*inner + c].  sign = -1 forward, +1 inverse (unnormalised).
-// tw4 != null applies the four-step twiddle exp(sign 2 pi i pos*o / L4) on load
-// (tw4_at_load = 1) or on store (0); tw4 holds exp(-2 pi i k / L4), k < L4.
+// tw4 != null: the contiguous rows of a 1-D four-step transform of length L4
+// (row o of a grid is k2 = o mod L4/L): the twiddle exp(sign 2 pi i pos k2 / L4)
+// is applied on load (forward) or on store (inverse), and only the modes
+// k2 + (L4/L) k1 = -band .. band (mod L4) are stored (forward) or read, the others
+// being zero (inverse).  tw4 holds exp(-2 pi i k / L4), k < L4.
 struct FftPass {
   int L;
   int64_t n_outer;
@@ -66,7 +69,7 @@ struct FftPass {
   int sign;
   const void* tw4 = nullptr;
   int64_t L4 = 0;
-  int tw4_at_load = 1;
+  int64_t band = 0;
   // Transform (o, c), o < n_outer, c < inner, reads element i at
   //   in + o in_os + (c / cp) in_cs + (c % cp) in_cs1 + (i / ip) in_es + (i % ip) in_es1
   // and writes element i at the same form over out (cp, ip = 1 or 2: pairs of

@@ -481,19 +481,6 @@ __global__ __launch_bounds__(kThreads) void mode_radial_1d_kernel(
   }
 }
 
-// 1-D four-step: zero the spectrum outside {-M..M} before the inverse transform.
-template <typename T>
-__global__ void zero_band_kernel(typename V2<T>::type* C, int64_t nf, int64_t L1, int64_t L2,
-                                 int64_t M, int npair) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nf * npair) return;
-  const int64_t idx = e % nf;
-  const int64_t k2 = idx / L1, k1 = idx % L1;
-  const int64_t k = k2 + L2 * k1;
-  const int64_t n = k <= nf / 2 ? k : k - nf;
-  if (n > M || n < -M) C[e] = typename V2<T>::type{T(0), T(0)};
-}
-
 template <typename T, int NK>
 void launch_mode_nk(Plan* P) {
   PhaseScope ps(P, PH_MODE);
@@ -620,16 +607,7 @@ void launch_mode(Plan* P) {
 #endif
 
 void GP_MIX_FN(Plan* P) {
-  using T = GP_MODE_T;
-  launch_mode<T>(P);
-  if (P->fourstep) {
-    const int npairs = P->npair * P->gv.nsets;
-    const int64_t tot = (int64_t)P->nf[0] * npairs;
-    hipLaunchKernelGGL(zero_band_kernel<T>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0,
-                       P->stream, static_cast<typename V2<T>::type*>(P->gv.C), (int64_t)P->nf[0],
-                       (int64_t)P->L1, (int64_t)P->L2, P->M, npairs);
-    GP_CHECK_LAUNCH();
-  }
+  launch_mode<GP_MODE_T>(P);
 }
 
 }  // namespace gp

@@ -794,23 +794,27 @@ void fft_all(Plan* P, int sign) {
   };
   if (d == 1 && P->fourstep) {
     const int L1 = P->L1, L2 = P->L2;
+    // rows l2 of the (L2 x L1) view that hold the active box: the only ones the
+    // forward transform reads and the inverse writes
+    const int l2a = P->lo[0] / L1, l2n = (P->lo[0] + P->na[0] - 1) / L1 - l2a + 1;
+    const size_t skip = (size_t)l2a * L1 * (fp64 ? 16 : 8);
     FftPass y;  // over l2 (stride L1)
     y.L = L2; y.n_outer = G; y.inner = L1; y.in_os = nf; y.out_os = nf;
     y.n_in = L2; y.in_start = 0; y.n_out = L2; y.out_start = 0; y.sign = sign;
     FftPass x;  // over l1 (contiguous), four-step twiddle
     x.L = L1; x.n_outer = G * L2; x.inner = 1; x.in_os = L1; x.out_os = L1;
     x.n_in = L1; x.in_start = 0; x.n_out = L1; x.out_start = 0; x.sign = sign;
-    x.tw4 = P->tw4.p; x.L4 = nf;
+    x.tw4 = P->tw4.p; x.L4 = nf; x.band = P->M;
     if (sign < 0) {
-      run(1, y, A, B, P->tw[1].p);
-      x.tw4_at_load = 1;
+      y.n_in = l2n; y.in_start = l2a;
+      run(1, y, static_cast<const char*>(A) + skip, B, P->tw[1].p);
       run(0, x, B, C, P->tw[0].p);
     } else {
       // the inverse result goes to C, not A: A keeps zeros outside the active
       // box (the spread writes only inside it) for the next forward pass
-      x.tw4_at_load = 0;
       run(0, x, C, B, P->tw[0].p);
-      run(1, y, B, C, P->tw[1].p);
+      y.n_out = l2n; y.out_start = l2a;
+      run(1, y, B, static_cast<char*>(C) + skip, P->tw[1].p);
     }
     return;
   }

@@ -7,8 +7,9 @@ the oracle, at sizes where tiles, remainders and window widths can go wrong.
 import numpy as np
 import pytest
 
+import oracle as O
 from paper_2407_03608_amd import inputs
-from tests.gpu_common import cuda, host, max_rel, say
+from tests.gpu_common import cuda, host, max_rel, oracle_params, say
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +61,25 @@ def test_interp_default_matches_per_bin(gp, d, n, M, tol, prec):
         e = max_rel(got, ref)
         say(f"interp d={d} n={n} w={info['w']} na={info['na']} prec={prec} clustered={clustered}: {e:.2e}")
         assert e <= (ORDER_FP32 if prec else ORDER_FP64), e
+
+
+@pytest.mark.parametrize("n,M,tol,prec", [
+    (150, 4200, 1e-8, 0), (150, 6200, 1e-8, 0), (90, 15000, 1e-8, 0), (60, 50000, 1e-8, 0),
+    (150, 4200, 1e-4, 1), (90, 33000, 1e-4, 1),
+])
+def test_four_step_against_oracle(gp, n, M, tol, prec):
+    """1-D grids over 8192 points: passes over rows of the active box and the
+    band of kept modes only, on splits L1 x L2 of several shapes.  A product
+    after another one (whose spectrum is still in the grids) has the same bits."""
+    prob = inputs.random_small(1, n, seed=M, nu=1.5, lmin=0.1, lmax=0.25)
+    P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, tol, precision=prec, M=M)
+    info = P.info()
+    assert info["nf"][0] > 8192
+    rng = np.random.default_rng(2)
+    a, b = rng.standard_normal(n), rng.standard_normal(n)
+    got = host(P.matvec(cuda(a)))
+    P.matvec(cuda(1e3 * b))
+    assert np.array_equal(got, host(P.matvec(cuda(a))))
+    e = max_rel(got, O.ktilde_matvec(oracle_params(info), prob.x, prob.sigma, prob.l, a))
+    say(f"four-step nf={info['nf'][0]} M={M} prec={prec}: {e:.2e}")
+    assert e <= (2e-4 if prec else 1e-6), e
