@@ -208,8 +208,8 @@ int gp_cg_solve(gp_plan_t plan, const double* y, double* alpha, int use_x0, doub
  * capture, tight serving loops, harnesses that forbid allocation): same
  * arguments, kernels, iterates and results as gp_cg_solve (bit for bit), but
  * it calls no hipMalloc, hipFree, hipHostMalloc or other allocating routine.
- * Its reduction scratch (512 per-block partial sums and 16 scalar slots,
- * 4.2 KB) is a static device array that each GPU holds for the life of the
+ * Its reduction scratch (2 x 512 per-block partial sums and 16 scalar slots,
+ * 8.3 KB) is a static device array that each GPU holds for the life of the
  * process, looked up on the first call on that device; every n fits in it (the
  * reduction never uses more than 512 blocks).  The plan's device must be the
  * current device (GP_EINVAL otherwise).  The host reads the solver's scalars

@@ -21,68 +21,97 @@ namespace {
 constexpr int kRedThreads = 256;
 constexpr int kRedBlocks = kCgBlocks;
 
+// Sum over the workgroup in a fixed order: shuffles within a wave, then the
+// waves' sums one after the other.  Valid in every thread.
+template <int NT>
 __device__ __forceinline__ double block_sum(double v) {
-  __shared__ double red[kRedThreads / 64];
+  __shared__ double red[NT / 64];
   for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  __syncthreads();  // an earlier sum's values have been read
   if (lane == 0) red[wid] = v;
   __syncthreads();
   double s = 0;
-  if (threadIdx.x == 0)
-    for (int k = 0; k < kRedThreads / 64; ++k) s += red[k];
-  return s;  // valid in thread 0
+  for (int k = 0; k < NT / 64; ++k) s += red[k];
+  return s;
 }
 
+// The kernels below serve one right-hand side or several in lockstep:
+// blockIdx.y is the column; column j of a vector argument starts at j n, its
+// partial sums at j kCgPart and its scalar slots at j kCgScalars, and every
+// column does the arithmetic of a solve of its own.
 __global__ __launch_bounds__(kRedThreads) void dot_partial(int64_t n, const double* __restrict__ a,
                                                            const double* __restrict__ b,
                                                            double* __restrict__ part) {
+  const int64_t col = blockIdx.y;
+  a += col * n;
+  b += col * n;
   double v = 0;
   for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kRedThreads)
     v += a[i] * b[i];
-  v = block_sum(v);
-  if (threadIdx.x == 0) part[blockIdx.x] = v;
+  v = block_sum<kRedThreads>(v);
+  if (threadIdx.x == 0) part[col * kCgPart + blockIdx.x] = v;
 }
 
-// S layout: 0 rr, 1 pAp, 2 rr_new, 3 bb, 4 beta, 5 scratch, 6 stopping
-// threshold on rr, 7 done flag, 8 completed iterations
-// mode 0: S[slot] = sum; mode 1 (rr update, skipped once done): S[2] = sum,
-// S[4] = sum / S[0], S[0] = sum, one more iteration, done if sum <= S[6]
-__global__ __launch_bounds__(kRedThreads) void dot_final(int nparts, const double* __restrict__ part,
-                                                         double* __restrict__ S, int slot, int mode) {
+// Sum of a dot product's partial sums, the same in every workgroup.
+__device__ __forceinline__ double part_sum(int nparts, const double* __restrict__ part) {
   double v = 0;
   for (int i = threadIdx.x; i < nparts; i += kRedThreads) v += part[i];
-  v = block_sum(v);
-  if (threadIdx.x == 0) {
-    if (mode == 0) {
-      S[slot] = v;
-    } else if (S[7] == 0.0) {
-      S[2] = v;
-      S[4] = v / S[0];
-      S[0] = v;
-      S[8] += 1.0;
-      if (v <= S[6]) S[7] = 1.0;
-    }
-  }
+  return block_sum<kRedThreads>(v);
 }
 
-__global__ void cg_init_flags(double* S, double stop2) {
-  if (threadIdx.x == 0) {
-    S[6] = stop2;
-    S[7] = 0.0;
-    S[8] = 0.0;
-  }
+// S layout: 0 rr, 3 bb, 5 scratch, 6 stopping threshold on rr, 7 done flag,
+// 8 completed iterations, 10 + k: rr at the start of iterations of parity k
+// S[slot] = sum of the partial sums
+__global__ __launch_bounds__(kRedThreads) void dot_final(int nparts, const double* __restrict__ part,
+                                                         double* __restrict__ S, int slot) {
+  const int64_t col = blockIdx.y;
+  const double v = part_sum(nparts, part + col * kCgPart);
+  if (threadIdx.x == 0) S[col * kCgScalars + slot] = v;
 }
 
-// x += a p ; r -= a Ap ; partial sums of r.r   with a = S[0]/S[1]
-__global__ __launch_bounds__(kRedThreads) void update_xr(int64_t n, const double* __restrict__ S,
+// per column: stopping threshold tol^2 ||b||^2, done at once if ||b|| = 0 or
+// the initial residual already meets it, no iterations yet
+__global__ void cg_init_flags(int m, double* S, double tol) {
+  const int col = blockIdx.x * blockDim.x + threadIdx.x;
+  if (col >= m) return;
+  double* s = S + (int64_t)col * kCgScalars;
+  s[6] = tol * tol * s[3];
+  s[7] = (s[3] == 0.0 || s[0] <= s[6]) ? 1.0 : 0.0;
+  s[8] = 0.0;
+  s[10] = s[0];
+}
+
+// The end of an iteration: rr = its new value, one more iteration, done if it
+// meets the threshold.  The next iteration's parity slot gets rr, so that no
+// workgroup that still reads the old one is in its way.
+__device__ __forceinline__ void cg_iteration_done(double* __restrict__ S, double rr, int parity) {
+  S[0] = rr;
+  S[10 + (parity ^ 1)] = rr;
+  S[8] += 1.0;
+  if (rr <= S[6]) S[7] = 1.0;
+}
+
+// x += a p ; r -= a Ap ; partial sums of r.r, with a = rr / p.Ap; every workgroup
+// sums p.Ap from its partial sums (a launch of its own for that sum costs 4.6 us:
+// an iteration's vector work at n = 2000 was 24 us in five launches, 14 in three)
+__global__ __launch_bounds__(kRedThreads) void update_xr(int64_t n, int nparts, int parity,
+                                                         const double* __restrict__ S,
+                                                         const double* __restrict__ part_pap,
                                                          double* __restrict__ x,
                                                          double* __restrict__ r,
                                                          const double* __restrict__ p,
                                                          const double* __restrict__ Ap,
                                                          double* __restrict__ part) {
+  const int64_t col = blockIdx.y;
+  S += col * kCgScalars;
   if (S[7] != 0.0) return;
-  const double a = S[0] / S[1];
+  x += col * n;
+  r += col * n;
+  p += col * n;
+  Ap += col * n;
+  const double a = S[10 + parity] / part_sum(nparts, part_pap + col * kCgPart);
   double v = 0;
   for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kRedThreads) {
@@ -91,18 +120,81 @@ __global__ __launch_bounds__(kRedThreads) void update_xr(int64_t n, const double
     r[i] = ri;
     v += ri * ri;
   }
-  v = block_sum(v);
-  if (threadIdx.x == 0) part[blockIdx.x] = v;
+  v = block_sum<kRedThreads>(v);
+  if (threadIdx.x == 0) part[col * kCgPart + blockIdx.x] = v;
 }
 
-// p = r + beta p, beta = S[4]
-__global__ void update_p(int64_t n, const double* __restrict__ S, const double* __restrict__ r,
-                         double* __restrict__ p) {
+// p = r + beta p, beta = (new rr, summed from its partial sums) / rr
+__global__ __launch_bounds__(kRedThreads) void update_p(int64_t n, int nparts, int parity, double* S,
+                                                        const double* __restrict__ part,
+                                                        const double* __restrict__ r,
+                                                        double* __restrict__ p) {
+  const int64_t col = blockIdx.y;
+  S += col * kCgScalars;
+  // the flag may be raised by this launch's first workgroup: p is then not used again
   if (S[7] != 0.0) return;
-  const double b = S[4];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
+  r += col * n;
+  p += col * n;
+  const double rr = part_sum(nparts, part + col * kCgPart);
+  const double b = rr / S[10 + parity];
+  for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * kRedThreads)
     p[i] = r[i] + b * p[i];
+  if (blockIdx.x == 0 && threadIdx.x == 0) cg_iteration_done(S, rr, parity);
+}
+
+// The three launches above in one, a workgroup per column, for vectors of at most
+// kSmallPer elements per thread, which are all loaded at once.  Bound by launches
+// and latency: one launch of 4 to 7 us for up to 4096 elements against three of
+// 12 together (at 8192 elements one workgroup takes 15).
+constexpr int kSmallThreads = 1024, kSmallPer = 4;
+constexpr int64_t kSmallN = (int64_t)kSmallThreads * kSmallPer;
+__global__ __launch_bounds__(kSmallThreads) void cg_step_small(int64_t n, int parity,
+                                                               double* S,
+                                                               double* __restrict__ x,
+                                                               double* __restrict__ r,
+                                                               double* __restrict__ p,
+                                                               const double* __restrict__ Ap) {
+  const int64_t col = blockIdx.y;
+  S += col * kCgScalars;
+  const double done = S[7], rr0 = S[10 + parity];
+  x += col * n;
+  r += col * n;
+  p += col * n;
+  Ap += col * n;
+  double pv[kSmallPer], av[kSmallPer], xv[kSmallPer], rv[kSmallPer];
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int64_t i = threadIdx.x + k * kSmallThreads;
+    const bool in = i < n;
+    pv[k] = in ? p[i] : 0.0;
+    av[k] = in ? Ap[i] : 0.0;
+    xv[k] = in ? x[i] : 0.0;
+    rv[k] = in ? r[i] : 0.0;
+  }
+  if (done != 0.0) return;
+  double v = 0;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) v += pv[k] * av[k];
+  const double a = rr0 / block_sum<kSmallThreads>(v);
+  v = 0;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    rv[k] -= a * av[k];
+    v += rv[k] * rv[k];
+  }
+  const double rr = block_sum<kSmallThreads>(v);
+  const double b = rr / rr0;
+#pragma unroll
+  for (int k = 0; k < kSmallPer; ++k) {
+    const int64_t i = threadIdx.x + k * kSmallThreads;
+    if (i < n) {
+      x[i] = xv[k] + a * pv[k];
+      r[i] = rv[k];
+      p[i] = rv[k] + b * pv[k];
+    }
+  }
+  if (threadIdx.x == 0) cg_iteration_done(S, rr, parity);  // the flag was read before the sums' barriers
 }
 
 // r = b - Ax
@@ -125,96 +217,6 @@ __global__ void copy_vec(int64_t n, const double* __restrict__ a, double* __rest
     b[i] = a[i];
 }
 
-// ------------------------------------------------- multiple right-hand sides --
-// The same kernels for m columns (blockIdx.y = column): column j of a vector
-// argument starts at j n, its partial sums at j kCgBlocks and its scalar
-// slots at j kCgScalars.  Every column does exactly the arithmetic of the
-// one-column kernels above.
-__global__ __launch_bounds__(kRedThreads) void dot_partial_m(int64_t n, const double* __restrict__ a,
-                                                             const double* __restrict__ b,
-                                                             double* __restrict__ part) {
-  const int64_t col = blockIdx.y;
-  a += col * n;
-  b += col * n;
-  double v = 0;
-  for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * kRedThreads)
-    v += a[i] * b[i];
-  v = block_sum(v);
-  if (threadIdx.x == 0) part[col * kRedBlocks + blockIdx.x] = v;
-}
-
-__global__ __launch_bounds__(kRedThreads) void dot_final_m(int nparts, const double* __restrict__ part,
-                                                           double* __restrict__ S, int slot, int mode) {
-  const int64_t col = blockIdx.y;
-  part += col * kRedBlocks;
-  S += col * kCgScalars;
-  double v = 0;
-  for (int i = threadIdx.x; i < nparts; i += kRedThreads) v += part[i];
-  v = block_sum(v);
-  if (threadIdx.x == 0) {
-    if (mode == 0) {
-      S[slot] = v;
-    } else if (S[7] == 0.0) {
-      S[2] = v;
-      S[4] = v / S[0];
-      S[0] = v;
-      S[8] += 1.0;
-      if (v <= S[6]) S[7] = 1.0;
-    }
-  }
-}
-
-// per column: stopping threshold tol^2 ||b||^2, done at once if ||b|| = 0 or
-// the initial residual already meets it, no iterations yet
-__global__ void cg_init_flags_m(int m, double* S, double tol) {
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= m) return;
-  double* s = S + (int64_t)col * kCgScalars;
-  s[6] = tol * tol * s[3];
-  s[7] = (s[3] == 0.0 || s[0] <= s[6]) ? 1.0 : 0.0;
-  s[8] = 0.0;
-}
-
-__global__ __launch_bounds__(kRedThreads) void update_xr_m(int64_t n, const double* __restrict__ S,
-                                                           double* __restrict__ x,
-                                                           double* __restrict__ r,
-                                                           const double* __restrict__ p,
-                                                           const double* __restrict__ Ap,
-                                                           double* __restrict__ part) {
-  const int64_t col = blockIdx.y;
-  S += col * kCgScalars;
-  if (S[7] != 0.0) return;
-  x += col * n;
-  r += col * n;
-  p += col * n;
-  Ap += col * n;
-  const double a = S[0] / S[1];
-  double v = 0;
-  for (int64_t i = (int64_t)blockIdx.x * kRedThreads + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * kRedThreads) {
-    x[i] += a * p[i];
-    const double ri = r[i] - a * Ap[i];
-    r[i] = ri;
-    v += ri * ri;
-  }
-  v = block_sum(v);
-  if (threadIdx.x == 0) part[col * kRedBlocks + blockIdx.x] = v;
-}
-
-__global__ void update_p_m(int64_t n, const double* __restrict__ S, const double* __restrict__ r,
-                           double* __restrict__ p) {
-  const int64_t col = blockIdx.y;
-  S += col * kCgScalars;
-  if (S[7] != 0.0) return;
-  r += col * n;
-  p += col * n;
-  const double b = S[4];
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = r[i] + b * p[i];
-}
-
 unsigned nblk(int64_t n) {
   int64_t b = (n + kRedThreads - 1) / kRedThreads;
   return (unsigned)std::min<int64_t>(std::max<int64_t>(b, 1), kRedBlocks);
@@ -224,7 +226,29 @@ void dot_into(Plan* P, const CgScratch& sc, const double* a, const double* b, in
   const unsigned nb = nblk(P->n);
   hipLaunchKernelGGL(dot_partial, dim3(nb), dim3(kRedThreads), 0, P->stream, P->n, a, b, sc.part);
   hipLaunchKernelGGL(dot_final, dim3(1), dim3(kRedThreads), 0, P->stream, (int)nb, sc.part, sc.S,
-                     slot, 0);
+                     slot);
+  GP_CHECK_LAUNCH();
+}
+
+// The vector work of one iteration after Ap for m columns (x, r, p, Ap: m
+// consecutive vectors).
+void cg_vectors(Plan* P, int m, int parity, const CgScratch& sc, double* x, double* r, double* p,
+                double* Ap) {
+  PhaseScope ps(P, PH_CG);
+  hipStream_t s = P->stream;
+  const int64_t n = P->n;
+  if (n <= kSmallN) {
+    hipLaunchKernelGGL(cg_step_small, dim3(1, m), dim3(kSmallThreads), 0, s, n, parity, sc.S, x, r, p, Ap);
+    GP_CHECK_LAUNCH();
+    return;
+  }
+  const unsigned nb = nblk(n);
+  const dim3 grid(nb, (unsigned)m);
+  hipLaunchKernelGGL(dot_partial, grid, dim3(kRedThreads), 0, s, n, p, Ap, sc.part);
+  hipLaunchKernelGGL(update_xr, grid, dim3(kRedThreads), 0, s, n, (int)nb, parity, sc.S, sc.part, x, r,
+                     p, Ap, sc.part + kCgBlocks);
+  hipLaunchKernelGGL(update_p, grid, dim3(kRedThreads), 0, s, n, (int)nb, parity, sc.S,
+                     sc.part + kCgBlocks, r, p);
   GP_CHECK_LAUNCH();
 }
 
@@ -319,7 +343,7 @@ int cg_solve_sorted_with(Plan* P, const CgScratch& sc, const double* b, double* 
     *rel_res = std::sqrt(rr / bb);
     return GP_OK;
   }
-  hipLaunchKernelGGL(cg_init_flags, dim3(1), dim3(64), 0, s, sc.S, stop2);
+  hipLaunchKernelGGL(cg_init_flags, dim3(1), dim3(64), 0, s, 1, sc.S, tol);
   GP_CHECK_LAUNCH();
   // Batches grow with the iteration count (at most 1/16 of the iterations
   // done so far are queued beyond convergence) and stay short when an
@@ -335,26 +359,25 @@ int cg_solve_sorted_with(Plan* P, const CgScratch& sc, const double* b, double* 
     for (int k = 0; k < batch; ++k) {
       ++queued;
       matvec_sorted(P, p, Ap, 1);
-      {
-        PhaseScope ps(P, PH_CG);
-        dot_into(P, sc, p, Ap, 1);
-        hipLaunchKernelGGL(update_xr, dim3(nb), dim3(kRedThreads), 0, s, n, sc.S, x,
-                           r, p, Ap, sc.part);
-        GP_CHECK_LAUNCH();
-      }
+      const int parity = (queued - 1) & 1;
       if (replace_every > 0 && queued % replace_every == 0) {
+        {
+          PhaseScope ps(P, PH_CG);
+          hipLaunchKernelGGL(dot_partial, dim3(nb), dim3(kRedThreads), 0, s, n, p, Ap, sc.part);
+          hipLaunchKernelGGL(update_xr, dim3(nb), dim3(kRedThreads), 0, s, n, (int)nb, parity, sc.S,
+                             sc.part, x, r, p, Ap, sc.part + kCgBlocks);
+          GP_CHECK_LAUNCH();
+        }
         matvec_sorted(P, x, Ap, 1);
+        PhaseScope ps(P, PH_CG);
         hipLaunchKernelGGL(residual, dim3(nb), dim3(kRedThreads), 0, s, n, b, Ap, r);
         hipLaunchKernelGGL(dot_partial, dim3(nb), dim3(kRedThreads), 0, s, n, r, r,
-                           sc.part);
+                           sc.part + kCgBlocks);
+        hipLaunchKernelGGL(update_p, dim3(nb), dim3(kRedThreads), 0, s, n, (int)nb, parity, sc.S,
+                           sc.part + kCgBlocks, r, p);
         GP_CHECK_LAUNCH();
-      }
-      {
-        PhaseScope ps(P, PH_CG);
-        hipLaunchKernelGGL(dot_final, dim3(1), dim3(kRedThreads), 0, s, (int)nb,
-                           sc.part, sc.S, 0, 1);
-        hipLaunchKernelGGL(update_p, dim3(nb), dim3(kRedThreads), 0, s, n, sc.S, r, p);
-        GP_CHECK_LAUNCH();
+      } else {
+        cg_vectors(P, 1, parity, sc, x, r, p, Ap);
       }
     }
     hs = read_S(P, sc, 9, tmp);
@@ -391,7 +414,7 @@ int cg_multi_sorted(Plan* P, int m, const double* b, double* x, double tol, int 
   rb.alloc((size_t)m * n * sizeof(double), s);
   pb.alloc((size_t)m * n * sizeof(double), s);
   apb.alloc((size_t)m * n * sizeof(double), s);
-  partb.alloc((size_t)m * kRedBlocks * sizeof(double), s);
+  partb.alloc((size_t)m * kCgPart * sizeof(double), s);
   Sb.alloc((size_t)m * kCgScalars * sizeof(double), s);
   double* r = rb.as<double>();
   double* p = pb.as<double>();
@@ -404,12 +427,13 @@ int cg_multi_sorted(Plan* P, int m, const double* b, double* x, double tol, int 
                                                   (int64_t)kRedBlocks * 64);
   hipLaunchKernelGGL(copy_vec, dim3(mn), dim3(kRedThreads), 0, s, (int64_t)m * n, b, r);
   hipLaunchKernelGGL(copy_vec, dim3(mn), dim3(kRedThreads), 0, s, (int64_t)m * n, r, p);
-  hipLaunchKernelGGL(dot_partial_m, grid, dim3(kRedThreads), 0, s, n, b, b, part);
-  hipLaunchKernelGGL(dot_final_m, dim3(1, m), dim3(kRedThreads), 0, s, (int)nb, part, S, 3, 0);
-  hipLaunchKernelGGL(dot_partial_m, grid, dim3(kRedThreads), 0, s, n, r, r, part);
-  hipLaunchKernelGGL(dot_final_m, dim3(1, m), dim3(kRedThreads), 0, s, (int)nb, part, S, 0, 0);
-  hipLaunchKernelGGL(cg_init_flags_m, dim3((m + 63) / 64), dim3(64), 0, s, m, S, tol);
+  hipLaunchKernelGGL(dot_partial, grid, dim3(kRedThreads), 0, s, n, b, b, part);
+  hipLaunchKernelGGL(dot_final, dim3(1, m), dim3(kRedThreads), 0, s, (int)nb, part, S, 3);
+  hipLaunchKernelGGL(dot_partial, grid, dim3(kRedThreads), 0, s, n, r, r, part);
+  hipLaunchKernelGGL(dot_final, dim3(1, m), dim3(kRedThreads), 0, s, (int)nb, part, S, 0);
+  hipLaunchKernelGGL(cg_init_flags, dim3((m + 63) / 64), dim3(64), 0, s, m, S, tol);
   GP_CHECK_LAUNCH();
+  const CgScratch sc{part, S, nullptr};
   std::vector<double> hS((size_t)m * kCgScalars);
   auto read_all = [&]() {
     GP_HIP(hipMemcpyAsync(hS.data(), S, hS.size() * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -431,13 +455,7 @@ int cg_multi_sorted(Plan* P, int m, const double* b, double* x, double tol, int 
     for (int k = 0; k < batch; ++k) {
       ++queued;
       matvec_multi_sorted(P, m, p, Ap, 1);
-      PhaseScope ps(P, PH_CG);
-      hipLaunchKernelGGL(dot_partial_m, grid, dim3(kRedThreads), 0, s, n, p, Ap, part);
-      hipLaunchKernelGGL(dot_final_m, dim3(1, m), dim3(kRedThreads), 0, s, (int)nb, part, S, 1, 0);
-      hipLaunchKernelGGL(update_xr_m, grid, dim3(kRedThreads), 0, s, n, S, x, r, p, Ap, part);
-      hipLaunchKernelGGL(dot_final_m, dim3(1, m), dim3(kRedThreads), 0, s, (int)nb, part, S, 0, 1);
-      hipLaunchKernelGGL(update_p_m, grid, dim3(kRedThreads), 0, s, n, S, r, p);
-      GP_CHECK_LAUNCH();
+      cg_vectors(P, m, (queued - 1) & 1, sc, x, r, p, Ap);
     }
     read_all();
     ms_per_iter = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0)
@@ -511,13 +529,27 @@ __global__ __launch_bounds__(kRedThreads) void gram_partial(int64_t n, const dou
   }
 }
 
-// G[e] = sum over blocks b (in order) of part[b][e]
-__global__ void gram_final(int nblocks, int ne, const double* __restrict__ part, double* __restrict__ G) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= ne) return;
+// G[e] = sum over blocks b of part[b][e]: 16 entries and 16 threads per entry in
+// a workgroup, each thread every 16th block in order, their sums added in order
+// (one thread per entry walks 512 dependent loads: 121 -> 6 us for 256 entries,
+// six times per block iteration)
+constexpr int kGramEnt = 16, kGramSplit = 16;
+__global__ __launch_bounds__(kGramEnt * kGramSplit) void gram_final(int nblocks, int ne,
+                                                                    const double* __restrict__ part,
+                                                                    double* __restrict__ G) {
+  __shared__ double sh[kGramSplit][kGramEnt];
+  const int le = threadIdx.x % kGramEnt, q = threadIdx.x / kGramEnt;
+  const int e = blockIdx.x * kGramEnt + le;
   double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += part[(int64_t)b * ne + e];
-  G[e] = s;
+  if (e < ne)
+    for (int b = q; b < nblocks; b += kGramSplit) s += part[(int64_t)b * ne + e];
+  sh[q][le] = s;
+  __syncthreads();
+  if (q == 0 && e < ne) {
+    double t = 0.0;
+    for (int k = 0; k < kGramSplit; ++k) t += sh[k][le];
+    G[e] = t;
+  }
 }
 
 // Row-local block updates with the coefficients co (np x m, row-major):
@@ -698,7 +730,8 @@ int cg_block_sorted(Plan* P, int m, const double* b, double* x, double tol, int 
   auto gram = [&](const double* U, int nu, const double* V, int nv, std::vector<double>& G) {
     hipLaunchKernelGGL(gram_partial, dim3(gram_blk), dim3(kRedThreads), 0, s, n, U, nu, V, nv,
                        partb.as<double>());
-    hipLaunchKernelGGL(gram_final, dim3((nu * nv + 255) / 256), dim3(256), 0, s, (int)gram_blk,
+    hipLaunchKernelGGL(gram_final, dim3((nu * nv + kGramEnt - 1) / kGramEnt),
+                       dim3(kGramEnt * kGramSplit), 0, s, (int)gram_blk,
                        nu * nv, partb.as<double>(), Gb.as<double>());
     GP_CHECK_LAUNCH();
     G.resize((size_t)nu * nv);

@@ -166,7 +166,7 @@ struct Plan : PlanRules {
   DevBuf vec;                 // fp64 scratch vectors for matvec / CG (sorted order)
   // CG reductions (allocated once per plan): per-block partial sums, the
   // scalar slots of the solver and a pinned host mirror of those slots
-  DevBuf cg_part;             // double [kCgBlocks]
+  DevBuf cg_part;             // double [kCgPart]
   DevBuf cg_S;                // double [kCgScalars]
   double* cg_hS = nullptr;    // pinned host, kCgScalars
   size_t device_bytes = 0;
@@ -267,10 +267,12 @@ void scatter_user(Plan* P, const double* x_sorted, double* x_user);
 
 // cg.hip
 // Device memory a CG solve reduces into: `part` holds one partial sum per
-// reduction block (kCgBlocks), `S` the solver's scalar slots (kCgScalars);
+// reduction block for two sums that are read and written by one launch (kCgPart =
+// 2 kCgBlocks), `S` the solver's scalar slots (kCgScalars);
 // hS is a pinned host mirror of S, or null (reads then go through a
 // synchronous copy to the stack).
 constexpr int kCgBlocks = 512;
+constexpr int kCgPart = 2 * kCgBlocks;
 constexpr int kCgScalars = 16;
 struct CgScratch {
   double* part;

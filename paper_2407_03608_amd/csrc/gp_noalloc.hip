@@ -18,7 +18,7 @@ namespace gp {
 
 // One copy per GPU, for the life of the process; every call on a GPU shares
 // it (concurrent calls on one GPU race on it).
-constexpr int kScratchDoubles = kCgBlocks + kCgScalars;
+constexpr int kScratchDoubles = kCgPart + kCgScalars;
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
 namespace {
@@ -61,15 +61,10 @@ extern "C" int gp_cg_solve_noalloc(gp_plan_t h, const double* y, double* alpha, 
     if (dev != P->device)
       throw Error{GP_EINVAL, "the plan's device (" + std::to_string(P->device) +
                                  ") must be current (current: " + std::to_string(dev) + ")"};
-    // The reduction uses min(ceil(n / 256), kCgBlocks) partial sums plus the
-    // scalar slots: at most kScratchDoubles doubles for every n.
-    const int64_t parts = std::min<int64_t>((P->n + 255) / 256, kCgBlocks);
-    if (parts + kCgScalars > kScratchDoubles)
-      throw Error{GP_EUNSUPPORTED, "CG scratch of " + std::to_string(parts + kCgScalars) +
-                                       " doubles exceeds the static " +
-                                       std::to_string(kScratchDoubles)};
+    // Each of the two sums uses min(ceil(n / 256), kCgBlocks) partial sums, so
+    // the array holds them and the scalar slots for every n.
     double* sp = device_scratch();
-    const CgScratch sc{sp, sp + kCgBlocks, nullptr};
+    const CgScratch sc{sp, sp + kCgPart, nullptr};
     const auto t0 = std::chrono::steady_clock::now();
     double* V = P->vec.as<double>();
     double* bs = V + 6 * P->n;

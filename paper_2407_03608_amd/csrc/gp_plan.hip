@@ -642,7 +642,7 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
              (d == 2 ? (size_t)(P->M / kModeTileX + 1) * (P->M / kModeTileY + 1) * sizeof(int) : 0);
   else
     bytes += (size_t)P->nt_eff * P->nk * (P->M + 1) * ts * 2;
-  bytes += (size_t)n * 8 * sizeof(double) + (kCgBlocks + kCgScalars) * sizeof(double);  // vectors
+  bytes += (size_t)n * 8 * sizeof(double) + (kCgPart + kCgScalars) * sizeof(double);  // vectors
   bytes += (size_t)nf * cs * 2;
   P->device_bytes = bytes;
   if (bytes_out) *bytes_out = bytes;
@@ -787,7 +787,7 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
   P->gv.nsets = 1;
   P->gv.cur = 0;
   P->vec.alloc((size_t)n * 8 * sizeof(double), P->stream);
-  P->cg_part.alloc(kCgBlocks * sizeof(double), P->stream);
+  P->cg_part.alloc(kCgPart * sizeof(double), P->stream);
   P->cg_S.alloc(kCgScalars * sizeof(double), P->stream);
   P->cg_hS = pinned_scalars_get();
   GP_HIP(hipStreamSynchronize(s));

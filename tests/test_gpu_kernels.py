@@ -83,3 +83,32 @@ def test_four_step_against_oracle(gp, n, M, tol, prec):
     e = max_rel(got, O.ktilde_matvec(oracle_params(info), prob.x, prob.sigma, prob.l, a))
     say(f"four-step nf={info['nf'][0]} M={M} prec={prec}: {e:.2e}")
     assert e <= (2e-4 if prec else 1e-6), e
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 1025, 4095, 4096, 4097, 5000])
+def test_cg_vector_kernels(gp, n):
+    """One launch per iteration up to 4096 points, three beyond: K iterations
+    against the same recurrence on the host with the plan's own products, and a
+    lockstep solve of two columns (bit for bit the single solves).  Bound: the
+    two recurrences differ by the rounding of sums of n terms, amplified over
+    K = 4 steps of a well-conditioned system (eta = 1)."""
+    prob = inputs.random_small(1, n, seed=n, nu=2.5, lmin=0.1, lmax=0.25, eta=1.0)
+    P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, 1e-8, M=60)
+    y = np.random.default_rng(n).standard_normal((2, n))
+    k = min(4, n)
+    got = [host(P.cg_solve(cuda(v), tol=1e-15, max_iter=k)[0]) for v in y]
+    both = host(P.cg_solve_multi(cuda(y), tol=1e-15, max_iter=k)[0])
+    for j in range(2):
+        assert np.array_equal(both[j], got[j])
+        x, r = np.zeros(n), y[j].copy()
+        p, rr = r.copy(), r @ r
+        for _ in range(k):
+            Ap = host(P.matvec(cuda(p), add_noise=True))
+            a = rr / (p @ Ap)
+            x += a * p
+            r -= a * Ap
+            rr, old = r @ r, rr
+            p = r + (rr / old) * p
+            if rr <= 1e-30 * (y[j] @ y[j]):
+                break
+        assert max_rel(got[j], x) < 1e-11, (n, j, max_rel(got[j], x))
