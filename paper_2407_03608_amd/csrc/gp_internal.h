@@ -93,27 +93,29 @@ struct Records {
   DevBuf cell;                // int32  [d][n] first window cell in the active box
   DevBuf pw;                  // T      [n][rs] window values and w_k
   DevBuf bin_start;           // int32  [n_bins + 1]
-  // Work lists that split crowded tiles into point chunks (built with the
-  // bin sort; see build_work_lists):
-  //  sp_work  int4 {tile, lo, hi, slot}: spread the tile's source points
-  //           [lo, hi) (positions in the tile's source sequence) into the
-  //           grid (slot < 0) or into partial tile `slot`
-  //  sp_red   int4 {tile, slot0, count, 0}: grid tile = sum of its partials,
-  //           added in slot order
+  // Work lists that split crowded bins into point chunks (built with the bin
+  // sort; see build_work_lists):
   //  in_work  int4 {bin, p_lo, p_hi, 0}: interpolate sorted points [p_lo, p_hi)
   //  in_work2 int4 {super-bin, lo, hi, 0} (d >= 2): interpolate positions
   //           [lo, hi) of the points of a 2x2(x1) block of bins (its two bin rows
   //           in order, each a contiguous range of the sorted points)
+  // and long sub-tile lists (built with the lists; empty when none is long):
+  //  sp_work  int4 {sub-tile, lo, hi, slot}: spread positions [lo, hi) of the
+  //           sub-tile's list into the grid (slot < 0) or into partial tile `slot`
+  //  sp_red   int4 {sub-tile, slot0, count, 0}: sub-tile = sum of its partials,
+  //           added in slot order
+  // (plans without lists: the same of tiles and positions in a tile's source
+  // sequence)
   DevBuf sp_work, sp_red, in_work, in_work2, part;
   int64_t n_sp_work = 0, n_sp_red = 0, n_in_work = 0, n_in_work2 = 0, n_slots = 0;
-  // Sub-tile spreading (fp32 grids, d >= 2; see build_spread_lists): sub-tiles
+  // Sub-tile spreading (see build_spread_lists): sub-tiles
   // of sub_st^d cells, numbered bin * (sub-tiles per bin) + sub, and for each
   // the points whose window reaches it, in visiting order:
   //  sub_off   int64 [n_sub + 1]   start of each sub-tile's list
   //  sub_list  int2 [sub_off[n_sub]]  {sorted index, first window cell
   //            relative to the sub-tile origin - (w - 1), 8 bits per dimension}
   DevBuf sub_off, sub_list;
-  int64_t n_sub = 0;
+  int64_t n_sub = 0, n_list = 0;  // sub-tiles, entries of all lists
   int sub_st = 0;
 };
 
@@ -140,6 +142,9 @@ struct Plan : PlanRules {
   DevBuf lr_off;              // int64 [a_rows + 1]: start of each row's factors in atab (step3 = 2)
   int lr_rank_max = 0;        // largest rank over the rows (step3 = 2)
   double lr_rank_mean = 0;
+  bool lean = false;          // no sub-tile lists (fp32 in d >= 2: unsplit lists): the byte
+                              // limit leaves no room for them
+  size_t lean_bytes = 0;      // device bytes of the plan in that form
   int spread_mode = GP_SPREAD_OWNER;  // resolved gp_opts.spread (never GP_SPREAD_AUTO)
   int interp_mode = 0;        // 0 default, 1 cache gather, 2 per-bin LDS tiles
   DevBuf atab;                // T [a_rows][nkp(nkp+1)/2] upper triangle of A_k'k(|n|^2)
@@ -224,7 +229,7 @@ void posterior_sorted(Plan* P, const double* x_sorted, int64_t m, const double* 
 // the grids of sum_i xs_i delta(x - x_i) over the points of R (sorted order)
 // through spreading, both FFTs and the mode mixing; interp_from_grid then
 // writes ys = K~(points of R', those points) xs for any record set R'.
-void forward_from(Plan* P, const Records& R, const double* xs);
+void forward_from(Plan* P, Records& R, const double* xs);
 void interp_from_grid(Plan* P, const Records& R, double* ys);
 // Kernel arguments of the spreading and interpolation kernels for one point
 // set (training points or targets) and one chunk of grid pairs.
@@ -237,7 +242,7 @@ struct NuArgs {
   int64_t pair_stride;
   int64_t grid_off;
   int g0, gc, nsrc;
-  int slot_pairs;  // grid pairs per partial tile slot (min(8, npair))
+  int n_slots;     // spreading: partial tiles of one vector (lists), grid pairs per partial tile (tiles)
   double eta2;
   int add_noise, first_chunk;
 };
@@ -248,15 +253,18 @@ void retag_plan_stream(Plan* P, hipStream_t st);
 // Grid A (spread output, interpolation input) of the current vector set.
 void* grid_a_current(const Plan* P);
 
-// Spreading in d >= 2 works on sub-tiles of spread_sub_side(P)^d cells, one
-// wavefront each, from per-sub-tile point lists built once per plan
-// (gp_spread.hip); other plans spread whole tiles.
-int spread_sub_side(const Plan* P);  // 0 when the plan spreads whole tiles
+// Spreading works on sub-tiles of spread_sub_side(P)^d cells, one wavefront
+// each, from per-sub-tile point lists built once per plan (gp_spread.hip),
+// unless the plan asks for the LDS-atomic variant or has no room for the lists
+// (then one workgroup per tile filters the tile's source bins).
+int spread_sub_side(const Plan* P);  // 0: no lists
 inline bool spread_uses_sub_tiles(const Plan* P) { return spread_sub_side(P) > 0; }
-// Device bytes of the sub-tile lists, bounded before the points are sorted.
-size_t spread_list_bound_bytes(const Plan* P, int64_t n);
+// Device bytes of the sub-tile lists (split: with the items and partial tiles of
+// long ones), bounded before the points are sorted.
+size_t spread_list_bound_bytes(const Plan* P, int64_t n, bool split);
 void build_spread_lists(Plan* P, Records& R);
-void spread_sub_launch(Plan* P, const Records& R, const double* xs);
+// xs: nsets consecutive vectors, into consecutive grid sets
+void spread_sub_launch(Plan* P, Records& R, const double* xs, int nsets);
 // out[0..n) = exclusive prefix sums of the counts in[0..n) (device arrays, on
 // stream s); *total = their sum, read back to the host.
 void exclusive_scan_counts(const int* in, int64_t n, int64_t* out, hipStream_t s, int64_t* total);

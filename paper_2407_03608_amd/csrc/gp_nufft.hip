@@ -1,6 +1,6 @@
 // The matvec y = K~ x of section 4.2 on gfx950.
 //
-//  step 1+2a  spread_kernel   c_{k,i} = w_k(x_i) x_i (eq:c) spread onto the fine
+//  step 1+2a  spread_list_kernel  c_{k,i} = w_k(x_i) x_i (eq:c) spread onto the fine
 //                             grids with the exponential-of-semicircle window
 //  step 2b    fft passes      forward FFT of every grid (pruned)
 //  step 3     mode_kernel     a_k'[n] = sum_j v~_j G^_k'j[n] sum_k G^_kj[n] b_k[n]
@@ -13,14 +13,9 @@
 // the imaginary part of complex grid g, so every FFT is complex-to-complex and
 // the mode kernel separates the two spectra with b(n) = (Z(n) + conj Z(-n))/2.
 //
-// Spreading is a gather: each workgroup owns one tile (or sub-tile) of the
-// active fine grid, collects every point whose window reaches it (the points
-// are bin-sorted by the tile of their first window cell, so the sources are
-// the 2^d (or more) neighbouring bins), and each thread sums the contributions
-// to the cells it owns in registers (owner-computes: no atomics, a fixed
-// summation order) before writing them with plain coalesced stores.  No global
-// atomics and no zero-fill pass.  An LDS-atomic variant (per-(point, row)
-// items) is kept as an option.
+// Spreading is a gather (gp_spread.hip): each wavefront owns one sub-tile of the
+// active fine grid and sums the points whose window reaches it in a fixed order.
+// An LDS-atomic variant (per-(point, row) items) is kept as an option.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -62,9 +57,10 @@ constexpr int kRG = 4;       // interpolation row groups per (point, grid pair)
 __host__ __device__ constexpr int lds_stride(int rs) { return rs | 1; }
 
 // ---------------------------------------------------------- spread (owner) ----
-// Owner-computes variant: each thread owns CPT cells of the tile and, for every
-// staged source point, adds its contribution to the grid pairs of the chunk in
-// registers when the point's window covers the cell.  No atomics, so the
+// Owner-computes without lists, for plans whose byte limit leaves no room for the
+// sub-tile lists (Plan::lean): each thread owns CPT cells of the tile and, for
+// every staged source point, adds its contribution to the grid pairs of the
+// chunk in registers when the point's window covers the cell.  No atomics, so the
 // summation order (and the result) is fixed.
 //
 // A crowded tile is split into chunks of its source points (work item
@@ -228,7 +224,7 @@ __global__ __launch_bounds__(kThreads) void spread_owner_kernel(
     if (slot >= 0) {
       const int l = threadIdx.x + c * kThreads;
 #pragma unroll
-      for (int g = 0; g < GC; ++g) part[((int64_t)slot * a.slot_pairs + g) * tcells + l] = acc[c][g];
+      for (int g = 0; g < GC; ++g) part[((int64_t)slot * a.n_slots + g) * tcells + l] = acc[c][g];
       continue;
     }
     const int64_t gi = a.grid_off + (int64_t)cx[c] * a.gstride[0] + (int64_t)cy[c] * a.gstride[1] +
@@ -260,7 +256,7 @@ __global__ __launch_bounds__(kThreads) void spread_reduce_kernel(
     const int g = e / tcells, l = e - g * tcells;
     V v = V{T(0), T(0)};
     for (int j = 0; j < wk.z; ++j) {
-      const V u = part[((int64_t)(wk.y + j) * a.slot_pairs + g) * tcells + l];
+      const V u = part[((int64_t)(wk.y + j) * a.n_slots + g) * tcells + l];
       v.x += u.x;
       v.y += u.y;
     }
@@ -626,6 +622,7 @@ template <typename T, int D, int CPT>
 void launch_spread_owner(Plan* P, const Records& R, const double* xs) {
   PhaseScope ps(P, PH_SPREAD);
   NuArgs a = nu_args(P, R);
+  a.n_slots = std::min(kGC, P->npair);  // grid pairs per partial tile
   const int gc = std::min(kGC, P->npair);
   const int nch = (P->npair + gc - 1) / gc;
   for (int ch = 0; ch < nch; ++ch) {
@@ -704,25 +701,31 @@ void launch_interp(Plan* P, const Records& R, const double* xs, double* ys, int 
   }
 }
 
+// The points of R for nsets consecutive vectors (into the grid sets from the
+// current one on).
 template <typename T>
-void spread_dispatch(Plan* P, const Records& R, const double* xs) {
-  const int tcells = P->tile[0] * P->tile[1] * P->tile[2];
-  const int mode = P->spread_mode;
-  // d >= 2: one wavefront per sub-tile from the point set's per-sub-tile lists
-  if (spread_uses_sub_tiles(P) && R.n_sub > 0) {
-    spread_sub_launch(P, R, xs);
+void spread_dispatch(Plan* P, Records& R, const double* xs, int nsets = 1) {
+  if (spread_uses_sub_tiles(P)) {  // one wavefront per sub-tile from the point set's lists
+    spread_sub_launch(P, R, xs, nsets);
     return;
   }
-  if (mode != GP_SPREAD_LDS_ATOMIC && tcells <= 2 * kThreads) {
-    const bool two = tcells > kThreads;
-    if (P->d == 1) two ? launch_spread_owner<T, 1, 2>(P, R, xs) : launch_spread_owner<T, 1, 1>(P, R, xs);
-    else if (P->d == 2) two ? launch_spread_owner<T, 2, 2>(P, R, xs) : launch_spread_owner<T, 2, 1>(P, R, xs);
-    else two ? launch_spread_owner<T, 3, 2>(P, R, xs) : launch_spread_owner<T, 3, 1>(P, R, xs);
-    return;
+  const bool owner = P->spread_mode != GP_SPREAD_LDS_ATOMIC;
+  const bool two = P->tile[0] * P->tile[1] * P->tile[2] > kThreads;  // at most 512 cells
+  const int cur = P->gv.cur;
+  for (int j = 0; j < nsets; ++j) {
+    P->gv.cur = cur + j;
+    if (owner) {
+      const double* x = xs + j * R.n;
+      if (P->d == 1) launch_spread_owner<T, 1, 1>(P, R, x);
+      else if (P->d == 2) launch_spread_owner<T, 2, 1>(P, R, x);
+      else two ? launch_spread_owner<T, 3, 2>(P, R, x) : launch_spread_owner<T, 3, 1>(P, R, x);
+      continue;
+    }
+    if (P->d == 1) launch_spread<T, 1>(P, R, xs + j * R.n);
+    else if (P->d == 2) launch_spread<T, 2>(P, R, xs + j * R.n);
+    else launch_spread<T, 3>(P, R, xs + j * R.n);
   }
-  if (P->d == 1) launch_spread<T, 1>(P, R, xs);
-  else if (P->d == 2) launch_spread<T, 2>(P, R, xs);
-  else launch_spread<T, 3>(P, R, xs);
+  P->gv.cur = cur;
 }
 
 template <typename T, int D, int WT>
@@ -931,7 +934,7 @@ void fft_all(Plan* P, int sign) {
 }
 
 template <typename T>
-void forward_and_mix(Plan* P, const Records& R, const double* xs) {
+void forward_and_mix(Plan* P, Records& R, const double* xs) {
   spread_dispatch<T>(P, R, xs);
   fft_all(P, -1);
   mix_modes(P);
@@ -964,7 +967,7 @@ NuArgs nu_args(const Plan* P, const Records& R) {
     a.grid_off = 0;
   }
   a.nsrc = P->nsrc;
-  a.slot_pairs = std::min(kGC, P->npair);
+  a.n_slots = 0;
   a.g0 = 0;
   a.gc = 0;
   a.eta2 = P->eta * P->eta;
@@ -1022,16 +1025,12 @@ void matvec_multi_sorted(Plan* P, int m, const double* xs, double* ys, int add_n
   P->gv.C = P->mC.p;
   P->gv.nsets = m;
   try {
-    const int64_t n = P->n;
-    for (int j = 0; j < m; ++j) {
-      P->gv.cur = j;
-      if (P->precision == GP_FP64) spread_dispatch<double>(P, P->rec, xs + j * n);
-      else spread_dispatch<float>(P, P->rec, xs + j * n);
-    }
+    P->gv.cur = 0;
+    if (P->precision == GP_FP64) spread_dispatch<double>(P, P->rec, xs, m);
+    else spread_dispatch<float>(P, P->rec, xs, m);
     fft_all(P, -1);
     mix_modes(P);
     fft_all(P, +1);
-    P->gv.cur = 0;
     if (P->precision == GP_FP64) interp_dispatch<double>(P, P->rec, xs, ys, add_noise, m);
     else interp_dispatch<float>(P, P->rec, xs, ys, add_noise, m);
   } catch (...) {
@@ -1065,7 +1064,7 @@ void posterior_sorted(Plan* P, const double* xs, int64_t m, const double* tpts,
 // Grids for the points of R weighted by xs (sorted order of R): spread,
 // forward FFT, mode mixing, inverse FFT.  interp_from_grid then evaluates the
 // result at the points of another record set of the same plan.
-void forward_from(Plan* P, const Records& R, const double* xs) {
+void forward_from(Plan* P, Records& R, const double* xs) {
   if (P->precision == GP_FP64)
     forward_and_mix<double>(P, R, xs);
   else

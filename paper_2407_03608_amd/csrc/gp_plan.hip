@@ -336,27 +336,33 @@ static int64_t source_total_bound(const Plan* P, int64_t n) {
 
 static int slot_pairs(const Plan* P) { return (int)std::min<int64_t>(8, P->npair); }
 
-// Device bytes of the work lists and partial tiles, bounded before the bin
-// sort is known (plan query) by the chunk-size rule.
-size_t work_list_bound_bytes(const Plan* P, int64_t n, size_t cs) {
+// Device bytes of the tiles' spread work and partial tiles (plans without
+// lists), bounded before the bin sort is known by the chunk-size rule.
+size_t tile_work_bound_bytes(const Plan* P, int64_t n, size_t cs) {
   const int64_t ts = source_total_bound(P, n);
   const int64_t qs = chunk_size(ts, P->n_bins, kMinSpreadChunk);
   const int64_t slots = 2 * ts / qs + 2;
   const int64_t tcells = (int64_t)P->tile[0] * P->tile[1] * P->tile[2];
   const int64_t items = P->n_bins + ts / qs + 1;
+  return (size_t)(2 * items) * 16 + (size_t)slots * tcells * slot_pairs(P) * cs;
+}
+
+// Device bytes of the interpolation work lists, bounded before the bin sort is
+// known (plan query) by the chunk-size rule.
+size_t work_list_bound_bytes(const Plan* P, int64_t n) {
   const int64_t qi = chunk_size(n, P->n_bins, kMinInterpChunk);
   const int64_t iitems = P->n_bins + n / qi + 1;
   const int64_t nsup = (int64_t)((P->nbins[0] + 1) / 2) * ((P->nbins[1] + 1) / 2) *
                        (P->d > 2 ? P->nbins[2] : 1);
   const int64_t sitems = P->d >= 2 ? nsup + n / chunk_size(n, nsup, kMinSuperChunk) + 1 : 0;
-  return (size_t)(2 * items + iitems + sitems) * 16 + (size_t)slots * tcells * slot_pairs(P) * cs;
+  return (size_t)(iitems + sitems) * 16;
 }
 
-// Build the spread and interpolation work lists from the bin offsets.  The
-// source sequence of a tile is the concatenation of its source bins in the
-// order the spread kernel visits them (offset q along each dimension, the
+// Build the spread work of a plan without lists: every tile's source points in
+// chunks.  The source sequence of a tile is the concatenation of its source bins
+// in the order the spread kernel visits them (offset q along each dimension, the
 // first dimension fastest; bins before the grid start are skipped).
-static void build_work_lists(Plan* P, Records& R, const std::vector<int>& start, size_t cs) {
+static void build_tile_work(Plan* P, Records& R, const std::vector<int>& start, size_t cs) {
   const int d = P->d, nsrc = P->nsrc;
   int nsrc_tot = 1;
   for (int r = 0; r < d; ++r) nsrc_tot *= nsrc;
@@ -402,6 +408,24 @@ static void build_work_lists(Plan* P, Records& R, const std::vector<int>& start,
     spr.insert(spr.end(), {(int)t, (int)slots, (int)c, 0});
     slots += c;
   }
+  hipStream_t s = P->stream;
+  R.n_sp_work = (int64_t)spw.size() / 4;
+  R.n_sp_red = (int64_t)spr.size() / 4;
+  R.n_slots = slots;
+  R.sp_work.alloc(spw.size() * sizeof(int), s);
+  GP_HIP(hipMemcpyAsync(R.sp_work.p, spw.data(), spw.size() * sizeof(int), hipMemcpyHostToDevice, s));
+  if (!spr.empty()) {
+    R.sp_red.alloc(spr.size() * sizeof(int), s);
+    GP_HIP(hipMemcpyAsync(R.sp_red.p, spr.data(), spr.size() * sizeof(int), hipMemcpyHostToDevice, s));
+    const int64_t tcells = (int64_t)P->tile[0] * P->tile[1] * P->tile[2];
+    R.part.alloc((size_t)slots * tcells * slot_pairs(P) * cs, s);
+  }
+  GP_HIP(hipStreamSynchronize(s));  // the host vectors are released on return
+}
+
+// Build the interpolation work lists from the bin offsets.
+static void build_work_lists(Plan* P, Records& R, const std::vector<int>& start) {
+  const int d = P->d;
   const int64_t qi = chunk_size(R.n, P->n_bins, kMinInterpChunk);
   std::vector<int> inw;
   for (int64_t b = 0; b < P->n_bins; ++b) {
@@ -442,18 +466,7 @@ static void build_work_lists(Plan* P, Records& R, const std::vector<int>& start,
     R.in_work2.alloc(inw2.size() * sizeof(int), P->stream);
     GP_HIP(hipMemcpyAsync(R.in_work2.p, inw2.data(), inw2.size() * sizeof(int), hipMemcpyHostToDevice, s));
   }
-  R.n_sp_work = (int64_t)spw.size() / 4;
-  R.n_sp_red = (int64_t)spr.size() / 4;
   R.n_in_work = (int64_t)inw.size() / 4;
-  R.n_slots = slots;
-  R.sp_work.alloc(spw.size() * sizeof(int), P->stream);
-  GP_HIP(hipMemcpyAsync(R.sp_work.p, spw.data(), spw.size() * sizeof(int), hipMemcpyHostToDevice, s));
-  if (!spr.empty()) {
-    R.sp_red.alloc(spr.size() * sizeof(int), P->stream);
-    GP_HIP(hipMemcpyAsync(R.sp_red.p, spr.data(), spr.size() * sizeof(int), hipMemcpyHostToDevice, s));
-    const int64_t tcells = (int64_t)P->tile[0] * P->tile[1] * P->tile[2];
-    R.part.alloc((size_t)slots * tcells * slot_pairs(P) * cs, P->stream);
-  }
   if (!inw.empty()) {
     R.in_work.alloc(inw.size() * sizeof(int), P->stream);
     GP_HIP(hipMemcpyAsync(R.in_work.p, inw.data(), inw.size() * sizeof(int), hipMemcpyHostToDevice, s));
@@ -504,10 +517,7 @@ void build_records_into(Plan* P, int64_t n, const double* pts, const double* sig
   const int64_t nch = std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, kSortCells / nbins));
   const int64_t chunk = (n + nch - 1) / nch;
   R.n = n;
-  // rows of 2-D plans that spread on sub-tiles are padded to 16 bytes (fp32:
-  // 4 values), so the spreading kernel reads them as 16-byte vectors
   R.rs = d * P->w + P->nkp;
-  if (d == 2 && spread_uses_sub_tiles(P)) R.rs = (R.rs + 3) / 4 * 4;
   R.perm.alloc(n * sizeof(int), P->stream);
   R.cell.alloc(n * d * sizeof(int), P->stream);
   R.pw.alloc((size_t)n * R.rs * tsz, P->stream);
@@ -538,7 +548,10 @@ void build_records_into(Plan* P, int64_t n, const double* pts, const double* sig
                         hipMemcpyDeviceToHost, s));
   GP_HIP(hipStreamSynchronize(s));
   if (out_of_box) *out_of_box = hbad;
-  build_work_lists(P, R, start, P->precision == GP_FP64 ? 16 : 8);
+  build_work_lists(P, R, start);
+  R.n_sp_work = R.n_sp_red = R.n_slots = 0;
+  if (spread_sub_side(P) == 0 && P->spread_mode != GP_SPREAD_LDS_ATOMIC)
+    build_tile_work(P, R, start, P->precision == GP_FP64 ? 16 : 8);
 #define GP_SCATTER(T)                                                                            \
   hipLaunchKernelGGL(scatter_records_kernel<T>, dim3(nb), dim3(bs), 0, s, d, n, P->w, P->beta, \
                      P->nk, P->nkp, R.rs, posd.as<int>(), cell_tmp.as<int>(),                  \
@@ -634,8 +647,7 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
   bytes += (size_t)G * (szA + szB + szB2 + szC) * cs;
   bytes += (size_t)n * (sizeof(int) * (1 + d) + ts * (d * P->w + P->nk + 1 + 3));
   bytes += (size_t)(P->n_bins + 1) * sizeof(int);
-  bytes += work_list_bound_bytes(P, n, cs);
-  bytes += spread_list_bound_bytes(P, n);
+  bytes += work_list_bound_bytes(P, n);
   if (P->step3 != 1)  // the low-rank rows (step3 = 2) hold at most the full row's size
     bytes += (size_t)P->a_rows * (P->nkp * (P->nkp + 1) / 2) * ts + rowmap.size() * sizeof(int) +
              (P->step3 == 2 ? (size_t)(P->a_rows + 1) * sizeof(int64_t) : 0) +
@@ -644,6 +656,17 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
     bytes += (size_t)P->nt_eff * P->nk * (P->M + 1) * ts * 2;
   bytes += (size_t)n * 8 * sizeof(double) + (kCgPart + kCgScalars) * sizeof(double);  // vectors
   bytes += (size_t)nf * cs * 2;
+  // The sub-tile lists of the spreading; where a byte limit leaves no room for
+  // them, tiles without lists (fp32 in d >= 2: lists that are not split)
+  const bool atomic = P->spread_mode == GP_SPREAD_LDS_ATOMIC;
+  const size_t base = bytes;
+  P->lean_bytes = base + tile_work_bound_bytes(P, n, cs) +
+                  (d >= 2 && P->precision == GP_FP32_BULK ? spread_list_bound_bytes(P, n, false) : 0);
+  bytes = atomic ? P->lean_bytes : base + spread_list_bound_bytes(P, n, true);
+  if (opts.max_device_bytes > 0 && bytes > opts.max_device_bytes) {
+    P->lean = true;
+    bytes = P->lean_bytes;
+  }
   P->device_bytes = bytes;
   if (bytes_out) *bytes_out = bytes;
   if (query_only) return GP_OK;

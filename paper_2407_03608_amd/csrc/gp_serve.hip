@@ -28,6 +28,7 @@ struct SRequest {
   double* alpha = nullptr;
   double nu = 0, eta = 0;
   size_t bytes = 0;
+  size_t limit64 = 0, limit32 = 0;  // byte limits of its plans (0: none)
   double t_submit = 0, t_start = -1, t_ready = -1, t_done = -1;
   int status = GP_OK, iters = 0, refinements = 0, slot = -1, precision = GP_FP64;
   double rel_res = 0;
@@ -70,27 +71,37 @@ void fill_opts(const Server& S, int bulk, hipStream_t st, gp_opts* o) {
   o->stream = st;
 }
 
-// Device bytes the request's plan(s) will hold; decides the precision path.
+// Device bytes the request's plan(s) will hold; decides the precision path (by
+// the fp64 plan without spreading lists, which hold more the denser the points)
+// and, where the plans with lists would never fit the budget, their limits.
 size_t request_bytes(Server& S, SRequest& r) {
   gp_opts o;
   size_t b64 = 0, b32 = 0;
   fill_opts(S, 0, S.qstream, &o);
   Plan q64;
   build_plan(r.d, r.n, r.pts, r.sigma, r.l, r.nu, r.eta, S.o.plan_tol, &o, &q64, true, &b64);
-  r.precision = (S.o.precision == GP_FP64 || b64 < S.o.fp64_below_bytes) ? GP_FP64 : GP_FP32_BULK;
-  if (r.precision == GP_FP64) return b64;
+  const size_t budget = S.o.max_device_bytes;
+  r.precision = (S.o.precision == GP_FP64 || q64.lean_bytes < S.o.fp64_below_bytes) ? GP_FP64 : GP_FP32_BULK;
+  if (r.precision == GP_FP64) {
+    if (b64 <= budget) return b64;
+    return r.limit64 = q64.lean_bytes;
+  }
   fill_opts(S, 1, S.qstream, &o);
   o.dw = q64.dw;
   o.M = q64.M;
   Plan q32;
   build_plan(r.d, r.n, r.pts, r.sigma, r.l, r.nu, r.eta, S.o.plan_tol_bulk, &o, &q32, true, &b32);
-  return b64 + b32;
+  if (b64 + b32 <= budget) return b64 + b32;
+  r.limit64 = q64.lean_bytes;
+  r.limit32 = q32.lean_bytes;
+  return r.limit64 + r.limit32;
 }
 
 void run_request(Server& S, SRequest& r, hipStream_t st) {
   GP_HIP(hipStreamWaitEvent(st, r.ready, 0));
   gp_opts o;
   fill_opts(S, 0, st, &o);
+  o.max_device_bytes = r.limit64;
   Plan P64;
   build_plan(r.d, r.n, r.pts, r.sigma, r.l, r.nu, r.eta, S.o.plan_tol, &o, &P64, false, nullptr);
   if (r.precision == GP_FP64) {
@@ -111,6 +122,7 @@ void run_request(Server& S, SRequest& r, hipStream_t st) {
   fill_opts(S, 1, st, &o);
   o.dw = P64.dw;
   o.M = P64.M;
+  o.max_device_bytes = r.limit32;
   Plan P32;
   build_plan(r.d, r.n, r.pts, r.sigma, r.l, r.nu, r.eta, S.o.plan_tol_bulk, &o, &P32, false, nullptr);
   r.t_ready = S.now();

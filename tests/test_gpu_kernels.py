@@ -112,3 +112,41 @@ def test_cg_vector_kernels(gp, n):
             if rr <= 1e-30 * (y[j] @ y[j]):
                 break
         assert max_rel(got[j], x) < 1e-11, (n, j, max_rel(got[j], x))
+
+
+@pytest.mark.parametrize("d,n,M,n_sigma,tol,prec", [
+    # 1 .. 12 grid pairs (one chunk of up to 8, two chunks, a chunk that overlaps the other)
+    (1, 700, 60, 1, 1e-8, 0), (1, 700, 5000, 23, 1e-8, 0), (1, 2500, 40, 17, 1e-4, 1), (1, 300, 6, 3, 1e-3, 1),
+    (2, 900, 24, 1, 1e-8, 0), (2, 900, 24, 13, 1e-8, 0), (2, 700, 20, 19, 1e-11, 0), (2, 5, 40, 5, 1e-4, 0),
+    (2, 900, 24, 1, 1e-4, 1), (2, 900, 24, 3, 1e-4, 1), (2, 900, 30, 9, 1e-6, 1), (2, 900, 30, 15, 1e-3, 1),
+    (3, 900, 8, 1, 1e-6, 0), (3, 500, 8, 11, 1e-9, 0), (3, 900, 8, 7, 1e-4, 1), (3, 900, 10, 21, 1e-5, 1),
+])
+def test_spread_lists_match_atomics(gp, d, n, M, n_sigma, tol, prec):
+    """Spreading from sub-tile lists by matrix instructions (whole and split
+    lists) against the LDS-atomic variant, uniform points and all in one cell."""
+    for clustered in (False, True):
+        prob = inputs.random_small(d, n, seed=3 * d + n_sigma, nu=1.5, lmin=0.1, lmax=0.25)
+        if clustered:  # lists longer than a chunk beside empty ones
+            rng = np.random.default_rng(n)
+            prob.x[: n - n // 4] = 0.37 + 1e-4 * rng.standard_normal((n - n // 4, d))
+            prob.x[0], prob.x[-1] = 0.0, 1.0
+        a = np.random.default_rng(2).standard_normal(n)
+        kw = dict(tol=tol, precision=prec, M=M, n_sigma=n_sigma)
+        got, info = _matvec(gp, prob, a, **kw)
+        ref, _ = _matvec(gp, prob, a, spread=1, **kw)
+        # without room for the lists: tiles that filter their source bins
+        lean, linfo = _matvec(gp, prob, a, max_device_bytes=info["device_bytes"] - 1, **kw) \
+            if _fits_lean(gp, prob, info, kw) else (got, info)
+        e, el = max_rel(got, ref), max_rel(lean, ref)
+        say(f"spread d={d} n={n} w={info['w']} pairs={info['n_pairs']} prec={prec} clustered={clustered}: "
+            f"{e:.2e}, lean {el:.2e} ({linfo['device_bytes']} of {info['device_bytes']} bytes)")
+        bar = ORDER_FP32 if prec else ORDER_FP64
+        assert e <= bar and el <= bar, (e, el)
+
+
+def _fits_lean(gp, prob, info, kw):
+    """Whether the plan without lists is the smaller one (dense points)."""
+    kw = dict(kw)
+    b = gp.plan_query(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, kw.pop("tol"),
+                      max_device_bytes=info["device_bytes"] - 1, **kw)
+    return b < info["device_bytes"]
