@@ -211,7 +211,7 @@ __device__ __forceinline__ void buf_store(double2 v, __amdgpu_buffer_rsrc_t r, u
 struct KParams {
   int64_t ntrans, inner, in_os, out_os, in_es, in_cs, out_es, out_cs;
   int64_t in_cs1, in_es1, out_cs1, out_es1;
-  int in_cps, in_ips, out_cps, out_ips;  // log2 of the interleave factors (0 or 1)
+  int in_cps, in_ips, out_cps, out_ips;  // log2 of the interleave factors
   int n_in, in_start, n_out, out_start, sign;
   // four-step passes (1-D): rows per grid, transform length, kept modes -M..M
   int tw4_mod, nf4, band;
@@ -219,8 +219,25 @@ struct KParams {
 
 // Element access of a pass: plain 64-bit addresses, buffer resources, or the
 // contiguous rows of a 1-D four-step transform (buffer resources, with its
-// twiddles and the band of kept modes).
-enum { kPlain = 0, kBuf = 1, kFour = 2 };
+// twiddles and the band of kept modes; kCols as kBuf for strided sequences).
+enum { kPlain = 0, kBuf = 1, kFour = 2, kCols = 3 };
+
+// Place of element pos of a sequence in the exchange buffer: one element of
+// padding every PU (rows: 32).  kCols: the B sequences of a workgroup are
+// interleaved, element pos of sequence b at lay(pos) B + b, and PU is the first
+// radix R1, so that lanes that hold B columns of consecutive j store at strides
+// (R1 + 1) B and load at strides B, both free of bank conflicts (one padded
+// buffer per sequence: d=3 M=189 fp64, L=768, 8 columns per workgroup 2.03 / 2.67 /
+// 2.67 / 1.97 -> 1.62 / 2.26 / 2.09 / 1.49 ms for the four strided passes; d=2
+// L=2048 fp64, 112 grids 2.22 / 1.67 -> 1.72 / 1.29).
+template <int PU>
+__device__ __forceinline__ constexpr int lay(int pos) { return pos + pos / PU; }
+// lay(base + off) for off known at compile time; whole: base is a multiple of PU
+template <int PU>
+__device__ __forceinline__ int lay_add(int base, int off, bool whole) {
+  return off % PU == 0 ? lay<PU>(base) + lay<PU>(off)
+                       : (whole && off < PU ? lay<PU>(base) + off : lay<PU>(base + off));
+}
 // four-step row k2, element k1 is mode k = k2 + L2 k1 (mod nf) of -M..M
 __device__ __forceinline__ bool four_kept(int k, const KParams& p) {
   return k <= p.band || k >= p.nf4 - p.band;
@@ -231,7 +248,7 @@ __device__ __forceinline__ bool four_kept(int k, const KParams& p) {
 // X[j + m L/R], twiddle exp(s 2 pi i k m / (Ls R)) (one table load, powers by
 // recurrence), outputs Y[(j - k) R + k + q Ls].  Then either exchange through
 // LDS into the next stage's inputs or, on the last stage, store.
-template <typename T, typename V, int L, int EPT, int Ls, int MODE>
+template <typename T, typename V, int L, int EPT, int B, int Ls, int MODE>
 __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
                                        const V* __restrict__ tw, int s, bool act, V* dst,
                                        int64_t dstride, const KParams& p, const V* tw4,
@@ -261,6 +278,8 @@ __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
     constexpr int R2 = next_radix(L / (Ls * R), EPT);
     static_assert(R2 > 0, "unsupported FFT length");
     constexpr int NB2 = EPT / R2;
+    constexpr int PU = MODE == kCols ? next_radix(L, EPT) : 32;
+    constexpr int BS = MODE == kCols ? B : 1;
 #pragma unroll
     for (int comp = 0; comp < 2; ++comp) {
 #pragma unroll
@@ -268,27 +287,28 @@ __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
         const int j = jt + TPT * u;
         const int k = j % Ls;
 #pragma unroll
-        for (int q = 0; q < R; ++q) buf[lpad((j - k) * R + k + q * Ls)] = comp ? v[u * R + q].y : v[u * R + q].x;
+        for (int q = 0; q < R; ++q)
+          buf[lay_add<PU>((j - k) * R + k, q * Ls, Ls == 1 && R % PU == 0) * BS] =
+              comp ? v[u * R + q].y : v[u * R + q].x;
       }
       __syncthreads();
-      // the read index is jt plus a compile-time c; where c is a multiple of
-      // 32, lpad(jt + c) = lpad(jt) + c + c/32, an immediate offset
-      const int rb = lpad(jt);
+      // the read index is jt plus a compile-time c: where c is a multiple of the
+      // padding unit, an immediate offset
 #pragma unroll
       for (int u = 0; u < NB2; ++u) {
-        const int j = jt + TPT * u;
+        constexpr bool kU = TPT % PU == 0;
 #pragma unroll
         for (int m = 0; m < R2; ++m) {
-          const int c = TPT * u + m * (L / R2);
-          const T val = (TPT % 32 == 0 && (L / R2) % 32 == 0) ? buf[rb + c + (c >> 5)]
-                                                             : buf[lpad(j + m * (L / R2))];
+          const int idx = kU ? lay_add<PU>(jt, TPT * u + m * (L / R2), false)
+                             : lay_add<PU>(jt + TPT * u, m * (L / R2), false);
+          const T val = buf[idx * BS];
           if (comp) v[u * R2 + m].y = val; else v[u * R2 + m].x = val;
         }
       }
       __syncthreads();
     }
-    stages<T, V, L, EPT, Ls * R, MODE>(v, buf, jt, tw, s, act, dst, dstride, p, tw4, row4, orsrc,
-                                      odl);
+    stages<T, V, L, EPT, B, Ls * R, MODE>(v, buf, jt, tw, s, act, dst, dstride, p, tw4, row4, orsrc,
+                                         odl);
   } else {
     // last stage: k = j, outputs at j + q L/R
     if (!act) return;
@@ -310,7 +330,7 @@ __device__ __forceinline__ void stages(V (&v)[EPT], T* __restrict__ buf, int jt,
         }
       return;
     }
-    if constexpr (MODE == kBuf) {
+    if constexpr (MODE == kBuf || MODE == kCols) {
       const int pm = (1 << p.out_ips) - 1;
       const int oes = (int)dstride, oes1 = (int)p.out_es1;
       const int i0 = jt - p.out_start;
@@ -363,7 +383,7 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
     KParams p) {
   using V = typename V2<T>::type;
   constexpr int TPT = L / EPT;
-  constexpr int LP = L + L / 32;
+  constexpr int LP = lay<MODE == kCols ? next_radix(L, EPT) : 32>(L);
   __shared__ T buf[B * LP];
   // Workgroups go to the 8 XCDs round-robin by id.  For strided (column)
   // passes, give each XCD a contiguous range of transforms so neighbouring
@@ -375,7 +395,8 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
     bid = x < r ? x * (q + 1) + slot : r * (q + 1) + (x - r) * q + slot;
   }
   int b, jt;
-  if (p.inner == 1) {
+  // rows: a sequence's threads are adjacent; columns: the sequences' are
+  if (MODE != kCols && (MODE != kPlain || p.in_es == 1)) {
     b = threadIdx.x / TPT;
     jt = threadIdx.x % TPT;
   } else {
@@ -417,7 +438,7 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
         for (int m = 0; m < R1; ++m)
           v[u * R1 + m] = cmul(v[u * R1 + m], tw4[(jt + TPT * u + m * (L / R1)) * row4]);
     }
-  } else if constexpr (MODE == kBuf) {
+  } else if constexpr (MODE == kBuf || MODE == kCols) {
     // line starts are non-decreasing in the transform index (checked on the
     // host), so the workgroup's first line is its lowest
     const int64_t t0 = bid * B;
@@ -455,8 +476,133 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
       v[u * R1 + m] = val;
     }
   }
-  stages<T, V, L, EPT, 1, MODE>(v, buf + b * LP, jt, tw, S, act, dst, p.out_es, p, tw4, row4,
+  stages<T, V, L, EPT, B, 1, MODE>(v, buf + (MODE == kCols ? b : b * LP), jt, tw, S, act, dst, p.out_es, p, tw4, row4,
                                orsrc, odl);
+}
+
+// ---------------------------------------------------------------- columns ----
+// NC adjacent columns per workgroup, all of them in every thread's registers
+// (v[c][..] is column c): a thread's loads of one row are adjacent, the columns
+// share the twiddles, and their exchanges go one after the other through one
+// LDS buffer of a single column.  The strided passes are bound by cache-line
+// requests, and this halves them.  d=2 N=1e6 fp64 (7 grids, M=2047, L=6144):
+// 1.04 -> 0.95 ms forward, 0.84 -> 0.87 inverse; fp32 0.35 -> 0.30 and 0.28 -> 0.26;
+// four fp32 columns 0.31 / 0.27; 3072-point fp64 columns lose (0.34 -> 0.36 and 0.22 ->
+// 0.27: two waves per SIMD instead of four).
+template <typename T, typename V, int L, int EPT, int NC, int Ls, int S>
+__device__ __forceinline__ void col_stages(V (&v)[NC][EPT], T* __restrict__ buf, int jt,
+                                           const V* __restrict__ tw, const KParams& p,
+                                           __amdgpu_buffer_rsrc_t orsrc, int ncol) {
+  constexpr int TPT = L / EPT;
+  constexpr int R = next_radix(L / Ls, EPT);
+  static_assert(R > 0, "unsupported FFT length");
+  constexpr int NB = EPT / R;
+  if constexpr (Ls > 1) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int k = (jt + TPT * u) % Ls;
+      V base = tw[k * (L / (Ls * R))];
+      if (S > 0) base.y = -base.y;
+      V wm = base;
+#pragma unroll
+      for (int m = 1; m < R; ++m) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c][u * R + m] = cmul(v[c][u * R + m], wm);
+        if (m + 1 < R) wm = cmul(wm, base);
+      }
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int u = 0; u < NB; ++u) Dft<T, V, R>::run(v[c] + u * R, S);
+  if constexpr (Ls * R < L) {
+    constexpr int R2 = next_radix(L / (Ls * R), EPT);
+    static_assert(R2 > 0, "unsupported FFT length");
+    constexpr int NB2 = EPT / R2;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int comp = 0; comp < 2; ++comp) {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          const int j = jt + TPT * u;
+          const int k = j % Ls;
+#pragma unroll
+          for (int q = 0; q < R; ++q)
+            buf[lpad((j - k) * R + k + q * Ls)] = comp ? v[c][u * R + q].y : v[c][u * R + q].x;
+        }
+        __syncthreads();
+        const int rb = lpad(jt);
+#pragma unroll
+        for (int u = 0; u < NB2; ++u) {
+          const int j = jt + TPT * u;
+#pragma unroll
+          for (int m = 0; m < R2; ++m) {
+            const int cc = TPT * u + m * (L / R2);
+            const T val = (TPT % 32 == 0 && (L / R2) % 32 == 0) ? buf[rb + cc + (cc >> 5)]
+                                                               : buf[lpad(j + m * (L / R2))];
+            if (comp) v[c][u * R2 + m].y = val; else v[c][u * R2 + m].x = val;
+          }
+        }
+        __syncthreads();
+      }
+    col_stages<T, V, L, EPT, NC, Ls * R, S>(v, buf, jt, tw, p, orsrc, ncol);
+  } else {
+    const int oes = (int)p.out_es, ocs = (int)p.out_cs;
+    const int i0 = jt - p.out_start;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          int i = i0 + TPT * u + q * (L / R);
+          i = i < 0 ? i + L : i;
+          buf_store(v[c][u * R + q], orsrc,
+                    i < p.n_out && c < ncol ? (unsigned)(c * ocs + i * oes) * (unsigned)sizeof(V) : kBufOut);
+        }
+  }
+}
+
+template <typename T, int L, int EPT, int NC, int S, int WV>
+__global__ __launch_bounds__(L / EPT, WV) void fft_cols_kernel(
+    const typename V2<T>::type* __restrict__ in, typename V2<T>::type* __restrict__ out,
+    const typename V2<T>::type* __restrict__ tw, KParams p) {
+  using V = typename V2<T>::type;
+  constexpr int TPT = L / EPT;
+  __shared__ T buf[L + L / 32];
+  int64_t bid = blockIdx.x;
+  {  // a contiguous range of columns per XCD
+    const int64_t nb = gridDim.x, q = nb / 8, r = nb % 8;
+    const int64_t x = bid % 8, slot = bid / 8;
+    bid = x < r ? x * (q + 1) + slot : r * (q + 1) + (x - r) * q + slot;
+  }
+  const int64_t ng = (p.inner + NC - 1) / NC;
+  const int64_t o = bid / ng, c0 = (bid - o * ng) * NC;
+  const int ncol = (int)min((int64_t)NC, p.inner - c0);
+  const int jt = threadIdx.x;
+  const V* ib = in + o * p.in_os + (c0 >> p.in_cps) * p.in_cs + (c0 & ((1 << p.in_cps) - 1)) * p.in_cs1;
+  V* ob = out + o * p.out_os + c0 * p.out_cs;
+  const __amdgpu_buffer_rsrc_t irsrc = buf_rsrc(ib);
+  const __amdgpu_buffer_rsrc_t orsrc = buf_rsrc(ob);
+  constexpr int R1 = next_radix(L, EPT);
+  constexpr int NB1 = EPT / R1;
+  V v[NC][EPT];
+  const int ies = (int)p.in_es;
+  const int i0 = jt - p.in_start;
+#pragma unroll
+  for (int u = 0; u < NB1; ++u)
+#pragma unroll
+    for (int m = 0; m < R1; ++m) {
+      int i = i0 + TPT * u + m * (L / R1);
+      i = i < 0 ? i + L : i;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        v[c][u * R1 + m] = buf_load(irsrc, i < p.n_in && c < ncol ? (unsigned)(i * ies + c) * (unsigned)sizeof(V) : kBufOut,
+                                    (V*)nullptr);
+    }
+  col_stages<T, V, L, EPT, NC, 1, S>(v, buf, jt, tw, p, orsrc, ncol);
 }
 
 constexpr int ept_for(int L) { return (L % 3 == 0) ? (L < 24 ? L : 24) : (L < 32 ? L : 32); }
@@ -482,13 +628,14 @@ bool buf_fits(const KParams& p, const FftPass& q, int B, int64_t vb) {
     // os) and at most B - 1 steps within one (each at most cs)
     int64_t span = (int64_t)(B - 1) * os;
     if (p.inner > 1) {
-      if (cps && cs1 > cs) return false;
-      const int64_t cmax = ((p.inner - 1) >> cps) * cs + (cps ? cs1 : 0);
+      const int64_t cin = ((int64_t)1 << cps) - 1;  // steps of cs1 within a group
+      if (cin * cs1 > cs) return false;
+      const int64_t cmax = ((p.inner - 1) >> cps) * cs + cin * cs1;
       if (os < cmax && p.ntrans > p.inner) return false;
       const int64_t k = (B - 1 + p.inner - 1) / p.inner;
       span = k * os + (int64_t)(B - 1) * cs;
     }
-    const int64_t emax = n > 0 ? ((int64_t)(n - 1) >> ips) * es + (ips ? es1 : 0) : 0;
+    const int64_t emax = n > 0 ? ((int64_t)(n - 1) >> ips) * es + (((int64_t)1 << ips) - 1) * es1 : 0;
     return (span + emax + 1) * vb < (int64_t)kBufRange - 64;
   };
   return side(p.in_os, p.in_cs, p.in_cs1, p.in_cps, p.in_es, p.in_es1, p.in_ips, p.n_in) &&
@@ -516,7 +663,12 @@ void launch_kernel(const FftPass& q, const KParams& p, const void* in, void* out
       throw Error{GP_EINVAL, "fft_pass: a four-step pass takes whole contiguous rows"};
     GP_FFT_GO(kFour);
   } else if (buf_fits(p, q, B, (int64_t)sizeof(V))) {
-    GP_FFT_GO(kBuf);
+    if constexpr (B > 1) {
+      if (p.in_es > 1) GP_FFT_GO(kCols);
+      else GP_FFT_GO(kBuf);
+    } else {
+      GP_FFT_GO(kBuf);
+    }
   } else {
     GP_FFT_GO(kPlain);
   }
@@ -525,6 +677,26 @@ void launch_kernel(const FftPass& q, const KParams& p, const void* in, void* out
 }
 
 constexpr int64_t kFewBlocks = 512;
+
+// NC columns per workgroup (see fft_cols_kernel); false where a workgroup's
+// offsets do not fit buffer addressing or NC columns are not adjacent in memory.
+template <typename T, int L, int EPT, int NC, int WV>
+bool launch_cols(const FftPass& q, const KParams& p, const void* in, void* out, const void* tw,
+                 hipStream_t s) {
+  using V = typename V2<T>::type;
+  if (q.tw4 != nullptr || q.inner < 2 || (1 << p.in_cps) % NC != 0 || p.in_cs1 != 1 || p.in_ips != 0 ||
+      p.out_cps != 0 || p.out_ips != 0 || !buf_fits(p, q, NC, (int64_t)sizeof(V)))
+    return false;
+  const dim3 g((unsigned)(q.n_outer * ((q.inner + NC - 1) / NC))), t(L / EPT);
+  const V *i = static_cast<const V*>(in), *w = static_cast<const V*>(tw);
+  V* o = static_cast<V*>(out);
+  if (p.sign < 0)
+    hipLaunchKernelGGL((fft_cols_kernel<T, L, EPT, NC, -1, WV>), g, t, 0, s, i, o, w, p);
+  else
+    hipLaunchKernelGGL((fft_cols_kernel<T, L, EPT, NC, 1, WV>), g, t, 0, s, i, o, w, p);
+  GP_CHECK_LAUNCH();
+  return true;
+}
 
 template <typename T, int L>
 void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hipStream_t s) {
@@ -543,10 +715,11 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
   p.in_es1 = q.in_es1;
   p.out_cs1 = q.out_cs1;
   p.out_es1 = q.out_es1;
-  p.in_cps = q.in_cp == 2;
-  p.in_ips = q.in_ip == 2;
-  p.out_cps = q.out_cp == 2;
-  p.out_ips = q.out_ip == 2;
+  auto log2i = [](int v) { return v <= 1 ? 0 : 31 - __builtin_clz((unsigned)v); };
+  p.in_cps = log2i(q.in_cp);
+  p.in_ips = log2i(q.in_ip);
+  p.out_cps = log2i(q.out_cp);
+  p.out_ips = log2i(q.out_ip);
   p.n_in = q.n_in;
   p.in_start = ((q.in_start % L) + L) % L;
   p.n_out = q.n_out;
@@ -569,34 +742,50 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
       return;
     }
   }
-  // 8192-point passes.  Rows (and fp64 columns): 16 elements per thread, 512
-  // threads, half the VGPRs of 32 per thread, so twice the waves per CU to
-  // cover the memory latency.  fp32 columns: four adjacent columns per
-  // workgroup (1024 threads, 32 elements each), so each quad of lanes reads 32
-  // contiguous bytes; the column passes are bound by cache-line requests per
-  // byte, and this wins (0.81 -> 0.72 ms) even though the 128-VGPR budget of a
-  // 1024-thread workgroup spills a few registers.
-  if constexpr (L == 8192) {
-    if constexpr (sizeof(T) == 4) {
-      if (q.inner > 1) {
-        launch_kernel<T, L, 32, 4>(q, p, in, out, tw, s);
-        return;
-      }
-    }
-    launch_kernel<T, L, 16, 1>(q, p, in, out, tw, s);
-  } else {
-    // Long strided (column) fp32 transforms: two columns per workgroup, so
-    // pairs of adjacent lanes read adjacent elements of one cache line.  fp64
-    // ones stay one per workgroup (two per workgroup: 1.56 against 1.47 ms for
-    // the forward column pass at d=2 N=1e6 with contiguous output).
-    if constexpr (B == 1 && L >= 6144) {
-      if (q.inner > 1 && sizeof(T) == 4) {
+  // 6144-point columns: two per workgroup in every thread's registers.
+  if constexpr (L == 6144) {
+    if (q.inner > 1 && p.in_es > 1 &&
+        launch_cols<T, L, EPT, 2, sizeof(T) == 8 ? 2 : 3>(q, p, in, out, tw, s))
+      return;
+    if constexpr (sizeof(T) == 4) {  // not adjacent: two on adjacent lanes
+      if (q.inner > 1 && p.in_es > 1) {
         launch_kernel<T, L, EPT, 2>(q, p, in, out, tw, s);
         return;
       }
     }
-    launch_kernel<T, L, EPT, B>(q, p, in, out, tw, s);
   }
+  // Powers of two: 16 elements per thread (16 x 16 x 8 ..) instead of 32, half the
+  // registers, so twice the waves per CU to cover the memory latency, for rows from
+  // 256 and strided passes from 1024 points (ms per pass with 32 -> 16: 7 fp64
+  // grids d=2 L=2048 rows 0.074 -> 0.063 and 0.105 -> 0.091, columns 0.128 -> 0.123,
+  // L=4096 columns 0.34 -> 0.33; d=3 fp32 L=512 rows 0.70 -> 0.62 and 0.87 -> 0.67).
+  // Strided passes of 256 and 512 points keep 32: one exchange less, with 8 and 16
+  // columns per workgroup (0.71 against 0.79 ms at L=512 fp64).  With 12 instead
+  // of 24, lengths with a factor 3 lose everywhere (L=768 fp64 rows 1.17 -> 1.31).
+  if constexpr ((L & (L - 1)) == 0 && L >= 256) {
+    if constexpr (L >= 1024) {
+      // fp32 columns of 8192: four adjacent ones per workgroup (1024 threads, 32
+      // elements each), so each quad of lanes reads 32 contiguous bytes; they are
+      // bound by cache-line requests per byte, and this wins (0.81 -> 0.72 ms) even
+      // though the 128-VGPR budget of a 1024-thread workgroup spills a few registers.
+      if constexpr (L == 8192 && sizeof(T) == 4) {
+        if (p.in_es > 1) {
+          launch_kernel<T, L, 32, 4>(q, p, in, out, tw, s);
+          return;
+        }
+      }
+      if (p.in_es > 1) {
+        launch_kernel<T, L, 16, L == 8192 ? 1 : B>(q, p, in, out, tw, s);
+        return;
+      }
+    }
+    if (p.in_es == 1) {
+      constexpr int BS = 256 / (L / 16) > 1 ? 256 / (L / 16) : 1;
+      launch_kernel<T, L, 16, BS>(q, p, in, out, tw, s);
+      return;
+    }
+  }
+  if constexpr ((L & (L - 1)) != 0 || L < 1024) launch_kernel<T, L, EPT, B>(q, p, in, out, tw, s);
 }
 
 template <typename T>
@@ -640,7 +829,7 @@ void fft_pass(int fp64, const FftPass& p, const void* in, void* out, const void*
   if (p.n_in > p.L || p.n_out > p.L || p.n_in < 0 || p.n_out < 0)
     throw Error{GP_EINVAL, "fft_pass: window longer than the transform"};
   for (int f : {p.in_cp, p.in_ip, p.out_cp, p.out_ip})
-    if (f != 1 && f != 2) throw Error{GP_EINVAL, "fft_pass: interleave factor must be 1 or 2"};
+    if (f < 1 || (f & (f - 1)) != 0) throw Error{GP_EINVAL, "fft_pass: interleave factors are powers of two"};
   if (fp64)
     dispatch<double>(p, in, out, twiddles, s);
   else

@@ -72,8 +72,8 @@ struct FftPass {
   int64_t band = 0;
   // Transform (o, c), o < n_outer, c < inner, reads element i at
   //   in + o in_os + (c / cp) in_cs + (c % cp) in_cs1 + (i / ip) in_es + (i % ip) in_es1
-  // and writes element i at the same form over out (cp, ip = 1 or 2: pairs of
-  // transforms or of elements interleaved).  es = 0 means inner (the sequence
+  // and writes element i at the same form over out (cp, ip powers of two:
+  // groups of transforms or of elements interleaved).  es = 0 means inner (the sequence
   // runs across the batch), cs = 0 means 1.
   int64_t in_es = 0, in_cs = 0, out_es = 0, out_cs = 0;
   int in_cp = 1, in_ip = 1, out_cp = 1, out_ip = 1;
@@ -145,6 +145,8 @@ struct Plan : PlanRules {
   bool lean = false;          // no sub-tile lists (fp32 in d >= 2: unsplit lists): the byte
                               // limit leaves no room for them
   size_t lean_bytes = 0;      // device bytes of the plan in that form
+  int blk2 = 1;               // 2-D: columns per block of grid B (see fft_all)
+  int64_t mp = 0;             // distance of rows of modes n_0 in grid C (3-D: in B and B2 too)
   int spread_mode = GP_SPREAD_OWNER;  // resolved gp_opts.spread (never GP_SPREAD_AUTO)
   int interp_mode = 0;        // 0 default, 1 cache gather, 2 per-bin LDS tiles
   DevBuf atab;                // T [a_rows][nkp(nkp+1)/2] upper triangle of A_k'k(|n|^2)

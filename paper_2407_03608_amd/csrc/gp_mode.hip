@@ -17,6 +17,7 @@ constexpr int kThreads = 256;
 struct ModeArgs {
   int d;
   int64_t M, mc, F;       // mc = 2M+1, F = mc^d
+  int64_t mp;             // distance of rows of modes
   int nk, npair, nt;
   int64_t pair_stride;
   int fourstep;
@@ -24,7 +25,7 @@ struct ModeArgs {
 };
 
 __device__ __forceinline__ int64_t mode_store(const ModeArgs& a, int64_t f, const int64_t* nv) {
-  if (!a.fourstep) return f;
+  if (!a.fourstep) return f % a.mc + (f / a.mc) * a.mp;
   int64_t k = nv[0] % a.nf;
   if (k < 0) k += a.nf;
   return (k % a.L2) * a.L1 + (k / a.L2);
@@ -116,6 +117,7 @@ __global__ __launch_bounds__(kThreads) void mode_kernel(
 struct RadialArgs {
   int d;
   int64_t M, mc, Q;       // Q = (M+1)^d orthant points
+  int64_t mp;             // distance of rows of modes
   int npair;
   int64_t pair_stride;
   int fourstep;
@@ -132,7 +134,7 @@ __device__ __forceinline__ int64_t radial_store(const RadialArgs& a, const int64
     int64_t f = 0, mul = 1;
     for (int r = 0; r < a.d; ++r) {
       f += (nv[r] + a.M) * mul;
-      mul *= a.mc;
+      mul *= r == 0 ? a.mp : a.mc;
     }
     return f;
   }
@@ -278,8 +280,8 @@ __global__ __launch_bounds__(kThreads) void mode_radial2_kernel(
   // pattern 1 negates n_1; it repeats pattern 0 when n_0 = 0 or n_1 = 0
   if (h == 1 && (an0 == 0 || an1 == 0)) return;
   const int64_t n1 = h ? -an1 : an1;
-  const int64_t st0 = (an0 + a.M) + (n1 + a.M) * a.mc;
-  const int64_t st1 = (-an0 + a.M) + (-n1 + a.M) * a.mc;
+  const int64_t st0 = (an0 + a.M) + (n1 + a.M) * a.mp;
+  const int64_t st1 = (-an0 + a.M) + (-n1 + a.M) * a.mp;
   for (int set = 0; set < a.nsets; ++set) {
     V* __restrict__ Cs = C + set * a.set_stride;
     V b[NK];
@@ -488,6 +490,7 @@ void launch_mode_nk(Plan* P) {
   a.d = P->d;
   a.M = P->M;
   a.mc = P->mcount;
+  a.mp = P->mp;
   a.F = 1;
   for (int r = 0; r < P->d; ++r) a.F *= a.mc;
   a.nk = P->nk;
@@ -497,7 +500,7 @@ void launch_mode_nk(Plan* P) {
   a.nf = P->nf[0];
   a.L1 = P->L1;
   a.L2 = P->L2;
-  a.pair_stride = P->fourstep ? P->nf[0] : a.F;
+  a.pair_stride = P->grid_elems[3];
   const int64_t half = (a.F + 1) / 2;
   for (int set = 0; set < P->gv.nsets; ++set) {
     hipLaunchKernelGGL((mode_kernel<T, NK>), dim3((unsigned)((half + kThreads - 1) / kThreads)),
@@ -515,6 +518,7 @@ void launch_radial_nk(Plan* P) {
   a.d = P->d;
   a.M = P->M;
   a.mc = P->mcount;
+  a.mp = P->mp;
   a.Q = 1;
   for (int r = 0; r < P->d; ++r) a.Q *= (P->M + 1);
   a.npair = P->npair;
@@ -522,9 +526,7 @@ void launch_radial_nk(Plan* P) {
   a.nf = P->nf[0];
   a.L1 = P->L1;
   a.L2 = P->L2;
-  int64_t F = 1;
-  for (int r = 0; r < P->d; ++r) F *= a.mc;
-  a.pair_stride = P->fourstep ? P->nf[0] : F;
+  a.pair_stride = P->grid_elems[3];
   a.nsets = P->gv.nsets;
   a.set_stride = P->npair * a.pair_stride;
   a.tiles = nullptr;

@@ -840,51 +840,52 @@ void fft_all(Plan* P, int sign) {
     // (column) pass writes whole sequences contiguously:
     //   forward: rows A[g][y][x] -> B; columns of B -> C[g][k0][k1]
     //   inverse: rows C[g][k0][.] -> B; columns of B -> A[g][y][x]
-    // fp32 grids hold pairs of sequences interleaved in B, B[g][y/2][k0][y%2]
-    // (forward) and B[g][k0/2][y][k0%2] (inverse): the column pass then reads
-    // 2 x 2 elements contiguously, and the row pass, which transforms two
-    // adjacent rows per workgroup, writes contiguously (fp32 FFT 1.24 ->
-    // 1.16 ms per matvec at d=2 N=1e6).  fp64 grids keep B[g][y][k0] and
-    // B[g][k0][y]: their two-row workgroups hold half the waves per CU
-    // (5.26 -> 5.58 ms interleaved).
-    // The mode kernel is symmetric in the two axes (it depends on |n|^2 and
-    // on the same deconvolution factor per axis), so it runs on C unchanged.
-    // B holds (na1 and mc rounded up to even) na1e x mce elements per pair.
-    const int64_t na0 = P->na[0], na1 = P->na[1], mce = mc + (mc & 1), na1e = na1 + (na1 & 1);
-    const bool ilv = !fp64;
-    const int64_t bstride = ilv ? na1e * mce : na1 * mc;  // elements of B per grid pair
-    FftPass r0;  // rows: two adjacent ones per workgroup when interleaved
+    // B holds blocks of blk2 = 8 columns, B[g][k0/8][y][k0%8] (forward) and
+    // B[g][y/8][k0][y%8] (inverse): a row pass writes 128 (fp64) or 64 (fp32)
+    // bytes at a time, and a column pass reads one stretch of memory whose cache
+    // lines belong to 8 columns, which run on one XCD.  The row passes are bound
+    // by the stores' segments, the column passes by cache-line requests: with
+    // blocks of 1, 2, 4, 8, 16 columns d=2 N=1e6 fp64 (L=6144, M=2047) forward rows
+    // take 1.39, 1.18, 0.77, 0.61, 0.61 ms and columns 0.70, 0.79, 0.94, 1.04, 1.05
+    // (unblocked 0.58 + 1.21), fp32 0.51, 0.37, 0.28, 0.22, 0.20 and 0.24, 0.31, 0.32,
+    // 0.35, 0.39; two columns per thread (fft_cols_kernel) then take the columns
+    // to 0.95 and 0.30.
+    // The mode kernel is symmetric in the two axes (it depends on |n|^2 and on
+    // the same deconvolution factor per axis), so it runs on C unchanged.
+    const int64_t na0 = P->na[0], na1 = P->na[1];
+    // blk2 = 1 (some lean plans) is the unblocked order B[g][y][k0], B[g][k0][y].
+    const int blk = P->blk2;
+    const int64_t bs = P->grid_elems[1];
+    FftPass r0;  // rows
     r0.L = nf; r0.sign = sign; r0.n_outer = G; r0.in_es = 1;
-    if (ilv) { r0.out_cp = 2; r0.out_cs1 = 1; r0.out_es = 2; } else { r0.out_es = 1; }
-    FftPass c1;  // strided sequences, contiguous output
+    r0.out_ip = blk; r0.out_es1 = 1; r0.out_os = bs;
+    FftPass c1;  // columns, contiguous output
     c1.L = nf; c1.sign = sign; c1.n_outer = G; c1.out_es = 1;
-    if (ilv) { c1.in_cs = 2; c1.in_ip = 2; c1.in_es1 = 1; } else { c1.in_cs = 1; }
+    c1.in_cp = blk; c1.in_cs1 = 1; c1.in_os = bs;
+    auto between = [&](int64_t rows, int64_t cols) {  // B holds rows x cols values
+      r0.out_cs = blk > 1 ? blk : cols;
+      r0.out_es = blk > 1 ? rows * blk : 1;
+      c1.in_cs = blk > 1 ? rows * blk : 1;
+      c1.in_es = blk > 1 ? blk : cols;
+    };
     if (sign < 0) {
+      between(na1, mc);
       r0.inner = na1; r0.in_os = na1 * na0; r0.in_cs = na0;
       r0.n_in = (int)na0; r0.in_start = P->lo[0];
-      r0.out_os = bstride; r0.out_cs = 2 * mce;
       r0.n_out = (int)mc; r0.out_start = (int)-P->M;
-      if (!ilv) {  // one contiguous row per transform
-        r0.inner = 1; r0.n_outer = G * na1; r0.in_os = na0; r0.in_cs = 0;
-        r0.out_os = mc; r0.out_cs = 0;
-      }
       run(0, r0, A, B, tw);
-      c1.inner = mc; c1.in_os = bstride; c1.in_es = ilv ? 2 * mce : mc;
+      c1.inner = mc;
       c1.n_in = (int)na1; c1.in_start = P->lo[1];
       c1.out_os = mc * mc; c1.out_cs = mc;
       c1.n_out = (int)mc; c1.out_start = (int)-P->M;
       run(1, c1, B, C, tw);
     } else {
+      between(mc, na1);
       r0.inner = mc; r0.in_os = mc * mc; r0.in_cs = mc;
       r0.n_in = (int)mc; r0.in_start = (int)-P->M;
-      r0.out_os = bstride; r0.out_cs = 2 * na1;
       r0.n_out = (int)na1; r0.out_start = P->lo[1];
-      if (!ilv) {
-        r0.inner = 1; r0.n_outer = G * mc; r0.in_os = mc; r0.in_cs = 0;
-        r0.out_os = na1; r0.out_cs = 0;
-      }
       run(1, r0, C, B, tw);
-      c1.inner = na1; c1.in_os = bstride; c1.in_es = ilv ? 2 * na1 : na1;
+      c1.inner = na1;
       c1.n_in = (int)mc; c1.in_start = (int)-P->M;
       c1.out_os = na1 * na0; c1.out_cs = na0;
       c1.n_out = (int)na0; c1.out_start = P->lo[0];
@@ -892,42 +893,39 @@ void fft_all(Plan* P, int sign) {
     }
     return;
   }
-  // d = 3: dimension-0 pass (contiguous) between A [.., na0] and B [.., mc]
+  // d = 3: dimension-0 pass (contiguous) between A [.., na0] and B [.., mp],
+  // dimension 1 between B [G][na2][na1][mp] and B2 [G][na2][mc][mp], dimension 2
+  // between B2 and C [G][mc][mc][mp].  Where mp rounds mc (odd) up to whole
+  // 128-byte lines, a workgroup's 8 (fp64) or 16 (fp32) columns are one line of
+  // each row.  The passes move 51 GB per product at d=3 M=189 fp64 in 9.7 ms,
+  // 4.0 to 4.4 TB/s against 4.7 of a copy.
+  const int64_t mp = P->mp;
   FftPass x;
   x.L = nf; x.inner = 1; x.sign = sign;
-  x.n_outer = G * P->na[1] * (d > 2 ? P->na[2] : 1);
-  // dimension-1 pass between B [G][na2][na1][mc] and B2/C [G][na2][mc][mc]
+  x.n_outer = G * P->na[1] * P->na[2];
   FftPass y;
-  y.L = nf; y.inner = mc; y.sign = sign;
-  y.n_outer = G * (d > 2 ? P->na[2] : 1);
+  y.L = nf; y.inner = mp; y.sign = sign;
+  y.n_outer = G * P->na[2];
+  FftPass z;
+  z.L = nf; z.inner = mc * mp; z.sign = sign; z.n_outer = G;
   if (sign < 0) {
     x.in_os = P->na[0]; x.n_in = P->na[0]; x.in_start = P->lo[0];
-    x.out_os = mc; x.n_out = (int)mc; x.out_start = (int)-P->M;
+    x.out_os = mp; x.n_out = (int)mc; x.out_start = (int)-P->M;
     run(0, x, A, B, tw);
-    y.in_os = P->na[1] * mc; y.n_in = P->na[1]; y.in_start = P->lo[1];
-    y.out_os = mc * mc; y.n_out = (int)mc; y.out_start = (int)-P->M;
-    if (d == 2) {
-      run(1, y, B, C, tw);
-    } else {
-      run(1, y, B, B2, tw);
-      FftPass z;
-      z.L = nf; z.inner = mc * mc; z.sign = sign; z.n_outer = G;
-      z.in_os = P->na[2] * mc * mc; z.n_in = P->na[2]; z.in_start = P->lo[2];
-      z.out_os = mc * mc * mc; z.n_out = (int)mc; z.out_start = (int)-P->M;
-      run(2, z, B2, C, tw);
-    }
+    y.in_os = P->na[1] * mp; y.n_in = P->na[1]; y.in_start = P->lo[1];
+    y.out_os = mc * mp; y.n_out = (int)mc; y.out_start = (int)-P->M;
+    run(1, y, B, B2, tw);
+    z.in_os = P->na[2] * mc * mp; z.n_in = P->na[2]; z.in_start = P->lo[2];
+    z.out_os = mc * mc * mp; z.n_out = (int)mc; z.out_start = (int)-P->M;
+    run(2, z, B2, C, tw);
   } else {
-    if (d == 3) {
-      FftPass z;
-      z.L = nf; z.inner = mc * mc; z.sign = sign; z.n_outer = G;
-      z.in_os = mc * mc * mc; z.n_in = (int)mc; z.in_start = (int)-P->M;
-      z.out_os = P->na[2] * mc * mc; z.n_out = P->na[2]; z.out_start = P->lo[2];
-      run(2, z, C, B2, tw);
-    }
-    y.in_os = mc * mc; y.n_in = (int)mc; y.in_start = (int)-P->M;
-    y.out_os = P->na[1] * mc; y.n_out = P->na[1]; y.out_start = P->lo[1];
-    run(1, y, d == 2 ? C : B2, B, tw);
-    x.in_os = mc; x.n_in = (int)mc; x.in_start = (int)-P->M;
+    z.in_os = mc * mc * mp; z.n_in = (int)mc; z.in_start = (int)-P->M;
+    z.out_os = P->na[2] * mc * mp; z.n_out = P->na[2]; z.out_start = P->lo[2];
+    run(2, z, C, B2, tw);
+    y.in_os = mc * mp; y.n_in = (int)mc; y.in_start = (int)-P->M;
+    y.out_os = P->na[1] * mp; y.n_out = P->na[1]; y.out_start = P->lo[1];
+    run(1, y, B2, B, tw);
+    x.in_os = mp; x.n_in = (int)mc; x.in_start = (int)-P->M;
     x.out_os = P->na[0]; x.n_out = P->na[0]; x.out_start = P->lo[0];
     run(0, x, B, A, tw);
   }

@@ -628,23 +628,40 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
   const size_t ts = cs / 2;
   int64_t szA = 1, szB = 1, szB2 = 0, szC = 1;
   const int64_t mc = P->mcount;
-  if (d == 1) {
-    szA = P->fourstep ? nf : P->na[0];
-    szB = P->fourstep ? nf : mc;
-    szC = P->fourstep ? nf : mc;
-  } else if (d == 2) {
-    szA = (int64_t)P->na[0] * P->na[1];
-    szB = (int64_t)(P->na[1] + (P->na[1] & 1)) * (mc + (mc & 1));  // pair-interleaved (see fft_all)
-    szC = mc * mc;
-  } else {
-    szA = (int64_t)P->na[0] * P->na[1] * P->na[2];
-    szB = (int64_t)P->na[2] * P->na[1] * mc;
-    szB2 = (int64_t)P->na[2] * mc * mc;
-    szC = mc * mc * mc;
-  }
   const int64_t G = P->npair;
+  // Grid layouts of the FFT passes (see fft_all): blocks of 8 columns in 2-D, rows
+  // of modes padded to whole 128-byte lines in large 3-D plans; a lean plan (below) takes
+  // as much of this as fits the bytes of pairs of columns and of unpadded rows.
+  auto grid_bytes = [&](bool lean) -> size_t {
+    P->mp = mc;
+    if (d == 1) {
+      szA = P->fourstep ? nf : P->na[0];
+      szB = szC = P->fourstep ? nf : mc;
+    } else if (d == 2) {
+      const int64_t na1 = P->na[1];
+      auto szb = [&](int64_t k) { return std::max(na1 * ((mc + k - 1) / k * k), (na1 + k - 1) / k * k * mc); };
+      const int64_t most = (na1 + (na1 & 1)) * (mc + 1);
+      P->blk2 = 8;
+      if (lean)
+        while (P->blk2 > 1 && (P->blk2 == 2 || szb(P->blk2) > most)) P->blk2 /= 2;
+      szA = P->na[0] * na1;
+      szB = lean ? most : szb(P->blk2);
+      szC = mc * mc;
+    } else {
+      // Padding pays where it adds little: d=3 fp64 M=189 (379 -> 384) a product
+      // takes 15.7 -> 15.0 ms, fp32 M=115 (231 -> 240) 8.03 -> 7.88; FFT passes at
+      // M=90 2.20 -> 2.12 (fp64, 1.7 % more), 0.83 -> 0.81 (fp32, 6 %), but at M=60
+      // 0.68 -> 0.70 (fp64, 5.8 %) and M=65 0.58 -> 0.59 (fp32, 10 %).
+      const int64_t line = 128 / (int64_t)cs, full = (mc + line - 1) / line * line;
+      if (!lean && mc >= 128 && (full - mc) * 16 <= mc) P->mp = full;
+      szA = (int64_t)P->na[0] * P->na[1] * P->na[2];
+      szB = (int64_t)P->na[2] * P->na[1] * P->mp;
+      szB2 = (int64_t)P->na[2] * mc * P->mp;
+      szC = mc * mc * P->mp;
+    }
+    return (size_t)G * (szA + szB + szB2 + szC) * cs;
+  };
   size_t bytes = 0;
-  bytes += (size_t)G * (szA + szB + szB2 + szC) * cs;
   bytes += (size_t)n * (sizeof(int) * (1 + d) + ts * (d * P->w + P->nk + 1 + 3));
   bytes += (size_t)(P->n_bins + 1) * sizeof(int);
   bytes += work_list_bound_bytes(P, n);
@@ -660,11 +677,13 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
   // them, tiles without lists (fp32 in d >= 2: lists that are not split)
   const bool atomic = P->spread_mode == GP_SPREAD_LDS_ATOMIC;
   const size_t base = bytes;
-  P->lean_bytes = base + tile_work_bound_bytes(P, n, cs) +
-                  (d >= 2 && P->precision == GP_FP32_BULK ? spread_list_bound_bytes(P, n, false) : 0);
-  bytes = atomic ? P->lean_bytes : base + spread_list_bound_bytes(P, n, true);
+  const size_t plain = tile_work_bound_bytes(P, n, cs) +
+                       (d >= 2 && P->precision == GP_FP32_BULK ? spread_list_bound_bytes(P, n, false) : 0);
+  P->lean_bytes = base + grid_bytes(true) + plain;
+  bytes = base + grid_bytes(false) + (atomic ? plain : spread_list_bound_bytes(P, n, true));
   if (opts.max_device_bytes > 0 && bytes > opts.max_device_bytes) {
     P->lean = true;
+    grid_bytes(true);
     bytes = P->lean_bytes;
   }
   P->device_bytes = bytes;
