@@ -733,9 +733,10 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
   // line is two workgroups per CU of the other form: below it those leave CUs
   // idle (d=1 N=2000, 12 grids of 192 x 256: 72 and 96 workgroups; with the
   // four-step rows' changes 0.015 / 0.022 / 0.026 / 0.018 -> 0.006 / 0.007 /
-  // 0.007 / 0.007 ms per pass).
+  // 0.007 / 0.007 ms per pass).  Other radices round differently: the sets of a batch
+  // are counted as one, so that each has the bits of a product of its own.
   if constexpr (L >= 64 && L <= 1024) {
-    if ((p.ntrans + B - 1) / B < kFewBlocks) {
+    if ((p.ntrans / q.nsets + B - 1) / B < kFewBlocks) {
       constexpr int ES = L % 3 == 0 ? 12 : 16;
       constexpr int BS = 64 / (L / ES) > 1 ? 64 / (L / ES) : 1;
       launch_kernel<T, L, ES, BS>(q, p, in, out, tw, s);

@@ -78,6 +78,7 @@ struct FftPass {
   int64_t in_es = 0, in_cs = 0, out_es = 0, out_cs = 0;
   int in_cp = 1, in_ip = 1, out_cp = 1, out_ip = 1;
   int64_t in_cs1 = 0, in_es1 = 0, out_cs1 = 0, out_es1 = 0;
+  int nsets = 1;  // vector sets among the transforms: the kernel is chosen for one of them
 };
 void fft_pass(int fp64, const FftPass& p, const void* in, void* out, const void* twiddles,
               hipStream_t s);

@@ -791,7 +791,8 @@ void fft_all(Plan* P, int sign) {
   FftPass q;
   q.sign = sign;
   // phase of a pass over dimension r
-  auto run = [&](int r, const FftPass& ps_, const void* in, void* out, const void* twp) {
+  auto run = [&](int r, FftPass ps_, const void* in, void* out, const void* twp) {
+    ps_.nsets = P->gv.nsets;
     PhaseScope sc(P, sign < 0 ? PH_FFT_FWD0 + r : PH_FFT_INV2 + (2 - r));
     fft_pass(fp64, ps_, in, out, twp, s);
   };

@@ -119,6 +119,31 @@ def test_fft_layouts(gp, d, M, tol, prec):
     assert e <= bar, e
 
 
+@pytest.mark.parametrize("d,M,n_sigma", [
+    # rows of 3, 10, 21, 36, 55, 105, 210 and 300 entries: whole and partial pieces and chunks
+    (2, 3, 1), (2, 40, 3), (2, 63, 5), (2, 64, 7), (2, 130, 9), (2, 65, 13), (2, 20, 19), (2, 31, 23),
+    (3, 3, 1), (3, 12, 3), (3, 16, 5), (3, 21, 7), (3, 9, 9), (3, 15, 13), (3, 8, 19), (3, 5, 23),
+])
+def test_mode_rows(gp, d, M, n_sigma):
+    """Step 3 with the table's rows staged through LDS against the direct sum over
+    the t nodes, and one vector against several (other step-3 kernels in 2-D, more
+    transforms per FFT pass): the same bits."""
+    n = 500
+    prob = inputs.random_small(d, n, seed=M + n_sigma, nu=1.5, lmin=0.1, lmax=0.25)
+    kw = dict(tol=1e-6, M=M, dw=0.2, n_sigma=n_sigma)
+    a = np.random.default_rng(4).standard_normal(n)
+    got, info = _matvec(gp, prob, a, **kw)
+    ref, _ = _matvec(gp, prob, a, step3=1, **kw)
+    e = max_rel(got, ref)
+    say(f"mode rows d={d} M={M} pairs={info['n_pairs']} t nodes={info['n_t']}: {e:.2e}")
+    # n_t N_sigma products in another order, cancellation among the w_k as above
+    assert e <= ORDER_FP64, e
+    P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, **kw)
+    A, _, _, _ = P.cg_solve_multi(cuda(np.stack([a, prob.y, -a])), tol=1e-14, max_iter=3)
+    a1, _ = P.cg_solve(cuda(prob.y), tol=1e-14, max_iter=3)
+    assert np.array_equal(host(A)[1], host(a1))
+
+
 @pytest.mark.parametrize("n", [1, 2, 1023, 1025, 4095, 4096, 4097, 5000])
 def test_cg_vector_kernels(gp, n):
     """One launch per iteration up to 4096 points, three beyond: K iterations
