@@ -250,7 +250,17 @@ __global__ __launch_bounds__(kThreads) void mode_radial_kernel(
   }
 }
 
-// d = 2: one thread per (orthant point, sign pattern), the two patterns of a
+// Grid pair (a_2g, a_2g+1) of one mode times the deconvolution D, packed for the modes n
+// and -n.  Written with explicit fma so that the kernels that call it round
+// alike: a column of several vector sets has the bits of a single product.
+template <typename V, typename T>
+__device__ __forceinline__ void pack_pair(V p, V q, T D, V* z, V* zc) {
+  const T px = p.x * D, py = p.y * D;
+  *z = V{__builtin_elementwise_fma(-q.y, D, px), __builtin_elementwise_fma(q.x, D, py)};
+  *zc = V{__builtin_elementwise_fma(q.y, D, px), __builtin_elementwise_fma(q.x, D, -py)};
+}
+
+// d = 2, several vector sets: one thread per (orthant point, sign pattern), the two patterns of a
 // point on adjacent lanes, so each reads the same row of A in the same load
 // instruction (one fetch) while holding half the registers of a thread that
 // owns both patterns.  Two blocks per orthant tile (two of its rows each).
@@ -263,18 +273,10 @@ __global__ __launch_bounds__(kThreads) void mode_radial2_kernel(
   const int h = (int)(threadIdx.x & 1);
   const int lp = (int)(threadIdx.x >> 1);
   const int64_t M1 = a.M + 1;
-  int64_t an0, an1;
-  if (a.tiles) {
-    const int64_t t = a.tiles[blockIdx.x >> 1];
-    an0 = (t % a.ntx) * kModeTileX + lp % kModeTileX;
-    an1 = (t / a.ntx) * kModeTileY + (kModeTileY / 2) * (blockIdx.x & 1) + lp / kModeTileX;
-    if (an0 > a.M || an1 > a.M) return;
-  } else {
-    const int64_t q = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 1;
-    if (q >= a.Q) return;
-    an0 = q % M1;
-    an1 = q / M1;
-  }
+  const int64_t t = a.tiles[blockIdx.x >> 1];
+  const int64_t an0 = (t % a.ntx) * kModeTileX + lp % kModeTileX;
+  const int64_t an1 = (t / a.ntx) * kModeTileY + (kModeTileY / 2) * (blockIdx.x & 1) + lp / kModeTileX;
+  if (an0 > a.M || an1 > a.M) return;
   const T* Ar = Atab + (int64_t)rowidx[an0 * an0 + an1 * an1] * NP;
   const T D = dec[an0] * dec[M1 + an1];
   // pattern 1 negates n_1; it repeats pattern 0 when n_0 = 0 or n_1 = 0
@@ -315,10 +317,159 @@ __global__ __launch_bounds__(kThreads) void mode_radial2_kernel(
 #pragma unroll
     for (int g = 0; g < NK / 2; ++g) {
       if (g >= a.npair) break;
-      const V pp = V{acc[2 * g].x * D, acc[2 * g].y * D};
-      const V qq = V{acc[2 * g + 1].x * D, acc[2 * g + 1].y * D};
-      Cs[g * a.pair_stride + st0] = V{pp.x - qq.y, pp.y + qq.x};
-      if (st1 != st0) Cs[g * a.pair_stride + st1] = V{pp.x + qq.y, -pp.y + qq.x};
+      V z, zc;
+      pack_pair(acc[2 * g], acc[2 * g + 1], D, &z, &zc);
+      Cs[g * a.pair_stride + st0] = z;
+      if (st1 != st0) Cs[g * a.pair_stride + st1] = zc;
+    }
+  }
+}
+
+// fp64, d = 2 and 3: a wave takes 64 / 2^(d-1) orthant points, a point's sign
+// patterns on adjacent lanes.  The rows of A it needs come through LDS, 128 bytes
+// of every row at a time: eight lanes load one row's 128 bytes (16 each), the next
+// chunk is in flight while the current one is used, and each lane then reads its
+// own row (slots permuted by the row so that the lanes fall on different banks).
+// The kernels above, whose lanes each gather their own row, are bound by the cache
+// lines looked up per load; this one by memory, 4.0 TB/s over the grid and
+// the table: d=3 M=189 (6 grid pairs) 3.66 -> 2.60 ms, d=2 M=2047 (7 pairs) 1.27 -> 1.20
+// ms, M=805 0.211 -> 0.202.  fp32 (segments of 256 bytes instead of 512 per
+// pattern) loses: d=2 M=2047 0.350 -> 0.373, d=3 M=115 0.223 -> 0.260; and so do several
+// vector sets in 2-D, whose row mode_radial2_kernel keeps in registers: 16
+// sets M=805 2.45 -> 2.96.  Taking the mirrored point (n_1, n_0), which shares the row,
+// on the same XCD at the same time changed nothing (1.19 and 0.206).
+template <typename T, int NK, int D>
+__global__ __launch_bounds__(kThreads) void mode_rows_kernel(
+    RadialArgs a, typename V2<T>::type* __restrict__ C, const T* __restrict__ Atab,
+    const int* __restrict__ rowidx, const T* __restrict__ dec) {
+  using V = typename V2<T>::type;
+  constexpr int E = 16 / (int)sizeof(T);  // table elements per 16-byte piece
+  typedef T Piece __attribute__((ext_vector_type(E)));
+  typedef T PieceU __attribute__((ext_vector_type(E), aligned(sizeof(T))));  // rows start at any element
+  constexpr int NP = NK * (NK + 1) / 2;
+  constexpr int PPR = (NP + E - 1) / E;     // pieces per row (the table ends with one to spare)
+  constexpr int NCH = (PPR + 7) / 8;        // chunks of 8 pieces
+  constexpr int NPAT = 1 << (D - 1), PW = 64 / NPAT;  // points per wave
+  constexpr int NLD = PW / 8;               // pieces loaded per lane and chunk
+  __shared__ Piece stage[kThreads / 64][PW * 8];
+  const int lane = (int)(threadIdx.x & 63);
+  const int h = lane % NPAT, rr = lane / NPAT;
+  const int lp = (int)threadIdx.x / NPAT;
+  const int64_t M1 = a.M + 1;
+  int64_t an[3] = {0, 0, 0};
+  bool act;
+  if (D == 2) {  // two blocks per orthant tile
+    const int64_t t = a.tiles[blockIdx.x >> 1];
+    an[0] = (t % a.ntx) * kModeTileX + lp % kModeTileX;
+    an[1] = (t / a.ntx) * kModeTileY + (kModeTileY / 2) * (blockIdx.x & 1) + lp / kModeTileX;
+    act = an[0] <= a.M && an[1] <= a.M;
+  } else {
+    int64_t q = (int64_t)blockIdx.x * (kThreads / NPAT) + lp;
+    act = q < a.Q;
+    an[0] = q % M1;
+    q /= M1;
+    an[1] = q % M1;
+    an[2] = q / M1;
+  }
+  if (!act) an[0] = an[1] = an[2] = 0;
+  const int row = rowidx[an[0] * an[0] + an[1] * an[1] + an[2] * an[2]];
+  const T* src[NLD];
+#pragma unroll
+  for (int i = 0; i < NLD; ++i) {
+    const int r = (lane >> 3) + 8 * i;  // the row of piece lane + 64 i
+    src[i] = Atab + (int64_t)__shfl(row, r * NPAT) * NP + ((lane & 7) ^ ((r >> 1) & 7)) * E;
+  }
+  T dd = dec[an[0]] * dec[M1 + an[1]];
+  if (D == 3) dd *= dec[2 * M1 + an[2]];
+  // pattern h negates the n_r whose bits are set; it repeats another pattern where
+  // one of those is zero or the point's first nonzero coordinate
+  int64_t nv[3];
+  const int first_nz = an[0] != 0 ? 0 : (an[1] != 0 ? 1 : 2);
+  nv[0] = an[0];
+#pragma unroll
+  for (int r = 1; r < D; ++r) {
+    const bool neg = (h >> (r - 1)) & 1;
+    if (neg && (an[r] == 0 || r == first_nz)) act = false;
+    nv[r] = neg ? -an[r] : an[r];
+  }
+  int64_t st0 = 0, st1 = 0, mul = 1;
+#pragma unroll
+  for (int r = 0; r < D; ++r) {
+    st0 += (nv[r] + a.M) * mul;
+    st1 += (a.M - nv[r]) * mul;
+    mul *= r == 0 ? a.mp : a.mc;
+  }
+  Piece* own = stage[threadIdx.x >> 6];
+  const Piece* mine = own + rr * 8;
+  const int swz = (rr >> 1) & 7;
+  for (int set = 0; set < a.nsets; ++set) {
+    V* __restrict__ Cs = C + set * a.set_stride;
+    // (a value the compiler cannot see through: it would otherwise load the whole row
+    // into registers ahead of the loop over sets)
+    int zero = 0;
+    int64_t r0 = st0, r1 = st1;
+    asm volatile("" : "+s"(zero), "+v"(r0), "+v"(r1));
+    Piece next[NLD];
+#pragma unroll
+    for (int i = 0; i < NLD; ++i)
+      if (8 <= PPR || (((lane & 7) ^ ((((lane >> 3) + 8 * i) >> 1) & 7)) < PPR))
+        next[i] = *reinterpret_cast<const PieceU*>(src[i] + zero);
+    V b[NK];
+#pragma unroll
+    for (int g = 0; g < NK / 2; ++g) {
+      const V z = Cs[g * a.pair_stride + r0], zc = Cs[g * a.pair_stride + r1];
+      b[2 * g] = V{T(0.5) * (z.x + zc.x) * dd, T(0.5) * (z.y - zc.y) * dd};
+      b[2 * g + 1] = V{T(0.5) * (z.y + zc.y) * dd, T(-0.5) * (z.x - zc.x) * dd};
+    }
+    V acc[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) acc[k] = V{T(0), T(0)};
+    int p = 0;
+    Piece cur;
+#pragma unroll
+    for (int k1 = 0; k1 < NK; ++k1) {
+#pragma unroll
+      for (int k2 = k1; k2 < NK; ++k2) {
+        if (p % (8 * E) == 0) {
+          const int ch = p / (8 * E);
+          // the sums so far are formed here: else the compiler puts them off and keeps the
+          // whole row in registers
+#pragma unroll
+          for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(acc[k].x), "+v"(acc[k].y));
+          __builtin_amdgcn_wave_barrier();
+#pragma unroll
+          for (int i = 0; i < NLD; ++i) own[lane + 64 * i] = next[i];
+          __builtin_amdgcn_wave_barrier();
+          if (ch + 1 < NCH) {
+#pragma unroll
+            for (int i = 0; i < NLD; ++i) {
+              const int pc = (ch + 1) * 8 + ((lane & 7) ^ ((((lane >> 3) + 8 * i) >> 1) & 7));
+              if ((ch + 2) * 8 <= PPR || pc < PPR)
+                next[i] = *reinterpret_cast<const PieceU*>(src[i] + zero + (ch + 1) * 8 * E);
+            }
+          }
+        }
+        if (p % E == 0) cur = mine[(p / E % 8) ^ swz];
+        const T av = cur[p % E];
+        ++p;
+        acc[k1].x += av * b[k2].x;
+        acc[k1].y += av * b[k2].y;
+        if (k2 != k1) {
+          acc[k2].x += av * b[k1].x;
+          acc[k2].y += av * b[k1].y;
+        }
+      }
+    }
+    if (!act) continue;
+    // (addresses formed again, not kept in registers since the loads)
+    int64_t w0 = st0, w1 = st1;
+    asm volatile("" : "+v"(w0), "+v"(w1));
+#pragma unroll
+    for (int g = 0; g < NK / 2; ++g) {
+      V z, zc;
+      pack_pair(acc[2 * g], acc[2 * g + 1], dd, &z, &zc);
+      Cs[g * a.pair_stride + w0] = z;
+      if (w1 != w0) Cs[g * a.pair_stride + w1] = zc;
     }
   }
 }
@@ -549,27 +700,28 @@ void launch_radial_nk(Plan* P) {
     }
     return;
   }
-  // fp64: 1.52 -> 1.43 ms at d=2 N=1e6; fp32 unchanged (0.37 ms), kept on
-  // the two-pattern kernel
   // 2-D: orthant tiles nearest the origin first (the table rows in use then
   // form a band that stays in the caches)
-  int64_t nblk = (a.Q + kThreads - 1) / kThreads;
-  if (P->d == 2 && P->mode_tiles.p) {
+  if (P->d == 2) {
     a.tiles = P->mode_tiles.as<int>();
     a.ntx = P->mode_ntx;
-    nblk = P->mode_ntx * (P->M / kModeTileY + 1);
   }
-  if (P->d == 2 && !a.fourstep && sizeof(T) == 8) {
-    hipLaunchKernelGGL((mode_radial2_kernel<T, NK>), dim3((unsigned)(a.tiles ? 2 * nblk : (2 * a.Q + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, P->stream, a, C, P->atab.as<T>(), P->rowidx.as<int>(),
-                       P->dec.as<T>());
+  // lanes: threads per orthant point
+  auto go = [&](auto kern, int lanes) {
+    const int64_t ppb = kThreads / lanes;
+    const int64_t nblk = P->d == 2 ? lanes * P->mode_ntx * (P->M / kModeTileY + 1) : (a.Q + ppb - 1) / ppb;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(kThreads), 0, P->stream, a, C, P->atab.as<T>(),
+                       P->rowidx.as<int>(), P->dec.as<T>());
     GP_CHECK_LAUNCH();
-    return;
+  };
+  // The measured sides of this rule are at mode_rows_kernel.
+  if constexpr (sizeof(T) == 8) {
+    if (P->d == 3) go(mode_rows_kernel<T, NK, 3>, 4);
+    else if (a.nsets == 1) go(mode_rows_kernel<T, NK, 2>, 2);
+    else go(mode_radial2_kernel<T, NK>, 2);
+  } else {
+    go(mode_radial_kernel<T, NK>, 1);
   }
-  hipLaunchKernelGGL((mode_radial_kernel<T, NK>), dim3((unsigned)nblk),
-                     dim3(kThreads), 0, P->stream, a, C,
-                     P->atab.as<T>(), P->d > 1 ? P->rowidx.as<int>() : nullptr, P->dec.as<T>());
-  GP_CHECK_LAUNCH();
 }
 
 template <typename T>

@@ -729,7 +729,7 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
     const int64_t tot = P->a_rows * npk;
     const unsigned nb = (unsigned)((tot + 255) / 256);
     if (P->step3 == 0) {
-      P->atab.alloc((size_t)tot * ts, P->stream);
+      P->atab.alloc((size_t)tot * ts + 16, P->stream);  // step 3 loads whole 16-byte pieces
       if (P->precision == GP_FP64)
         hipLaunchKernelGGL(atab_kernel<double>, dim3(nb), dim3(256), 0, s, P->a_rows, npk, P->nkp,
                            P->nk, P->nt_eff, dsv.as<double>(), dtau.as<double>(), dcst.as<double>(),
