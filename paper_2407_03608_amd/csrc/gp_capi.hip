@@ -73,6 +73,9 @@ Plan::~Plan() {
     (void)hipEventDestroy(ev.b);
   }
   for (auto e : pool) (void)hipEventDestroy(e);
+  if (side_in) (void)hipEventDestroy(side_in);
+  if (side_out) (void)hipEventDestroy(side_out);
+  if (side) (void)hipStreamDestroy(side);
 }
 
 // Iterative refinement in the caller's point order (the two plans may sort the
@@ -413,10 +416,10 @@ int gp_posterior_mean(gp_plan_t h, const double* alpha, int64_t m, const double*
     if (!h || !alpha || !targets || !sigma_t || !l_t || !mu) throw Error{GP_EINVAL, "null argument"};
     if (m < 1) throw Error{GP_EINVAL, "m must be >= 1"};
     Plan* P = &h->P;
-    validate_targets(P, m, targets, sigma_t, l_t);
     double* xs = P->vec.as<double>();
     gather_sorted(P, alpha, xs);
-    posterior_sorted(P, xs, m, targets, sigma_t, l_t, mu);
+    posterior_sorted(P, xs, m, targets, sigma_t, l_t, mu,
+                     [&] { validate_targets(P, m, targets, sigma_t, l_t); });
     return GP_OK;
   });
 }

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <string>
+#include <functional>
 #include <vector>
 
 #include "../../include/gpnufft.h"
@@ -186,6 +187,10 @@ struct Plan : PlanRules {
   };
   std::vector<Ev> events;
   std::vector<hipEvent_t> pool;
+  // posterior mean: the targets' records are built here while the forward pass
+  // runs on the plan's stream (created at the first call)
+  hipStream_t side = nullptr;
+  hipEvent_t side_in = nullptr, side_out = nullptr;
   ~Plan();
 };
 
@@ -224,9 +229,11 @@ void matvec_multi_sorted(Plan* P, int m, const double* x_sorted, double* y_sorte
 // Largest m for which the batched grids fit in half of the free device memory.
 int multi_capacity(Plan* P, int want);
 // Evaluate the type-2 + combine step at arbitrary mapped targets after a forward
-// pass of x_sorted; used by the posterior mean.
+// pass of x_sorted; used by the posterior mean.  check validates the targets
+// (throws), on the stream that is the plan's when it is called.
 void posterior_sorted(Plan* P, const double* x_sorted, int64_t m, const double* tpts,
-                      const double* tsig, const double* tl, double* mu);
+                      const double* tsig, const double* tl, double* mu,
+                      const std::function<void()>& check);
 // gather / scatter between caller and sorted order
 // K~ between record sets of one plan (same grid and box): forward_from puts
 // the grids of sum_i xs_i delta(x - x_i) over the points of R (sorted order)

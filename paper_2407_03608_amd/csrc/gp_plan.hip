@@ -539,7 +539,6 @@ void build_records_into(Plan* P, int64_t n, const double* pts, const double* sig
     hipLaunchKernelGGL(sort_place_kernel, dim3((unsigned)nch), dim3(kSortBatch), 0, s, n, chunk, nch,
                        bin_of.as<int>(), off.as<unsigned long long>(), posd.as<int>());
     GP_CHECK_LAUNCH();
-    GP_HIP(hipStreamSynchronize(s));  // cnt and off are released here
   }
   int hbad = 0;
   std::vector<int> start(P->n_bins + 1, 0);
@@ -564,7 +563,6 @@ void build_records_into(Plan* P, int64_t n, const double* pts, const double* sig
     GP_SCATTER(float);
 #undef GP_SCATTER
   GP_CHECK_LAUNCH();
-  GP_HIP(hipStreamSynchronize(s));
 }
 
 // ------------------------------------------------------------ build_plan ----

@@ -209,3 +209,36 @@ def _fits_lean(gp, prob, info, kw):
     b = gp.plan_query(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, kw.pop("tol"),
                       max_device_bytes=info["device_bytes"] - 1, **kw)
     return b < info["device_bytes"]
+
+
+@pytest.mark.parametrize("d,n,m,prec", [(1, 300, 1, 0), (2, 3000, 5000, 0), (2, 900, 40, 1), (3, 500, 300, 0)])
+def test_posterior_mean_streams(gp, d, n, m, prec):
+    """The targets are read on a stream beside the plan's: they may be written by
+    work still queued on the plan's stream, and after a refused call the
+    plan gives the same bits as before."""
+    import torch
+    prob = inputs.random_small(d, n, seed=5 * d, nu=1.5, lmin=0.1, lmax=0.25)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, 1e-6 if prec == 0 else 1e-4,
+                    precision=prec, M={1: 100, 2: 40, 3: 12}[d])
+        i = np.random.default_rng(6).integers(0, n, m)
+        true = [cuda(v[i]) for v in (prob.x, prob.sigma, prob.l)]
+        al = cuda(np.random.default_rng(7).standard_normal(n))
+        s.synchronize()
+        want = host(P.posterior_mean(al, *true))
+        work = torch.rand(2048, 2048, device="cuda")
+        for _ in range(3):
+            t = [v.clone() for v in true]
+            t[0].fill_(0.5)
+            s.synchronize()
+            for _ in range(20):
+                work = work @ work
+                work = work / work.abs().max()
+            t[0].copy_(true[0])
+            got = P.posterior_mean(al, *t)
+            assert np.array_equal(host(got), want)
+            bad = true[0].clone()
+            bad[m // 2, 0] = 7.0
+            with pytest.raises(gp.GpError):
+                P.posterior_mean(al, bad, *true[1:])
