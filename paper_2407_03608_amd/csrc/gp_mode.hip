@@ -594,14 +594,25 @@ __global__ __launch_bounds__(kThreads) void mode_radial_1d_kernel(
   __shared__ V sb[PPB][NK];
   __shared__ V sa[PPB][NK];
   const int lp = threadIdx.x / NK, j = threadIdx.x % NK;
-  const int64_t n0 = (int64_t)blockIdx.x * PPB + lp;
-  const bool act = lp < PPB && n0 <= a.M;
+  // Four-step grids hold mode k = k2 + L2 k1 at k2 L1 + k1: the points are dealt along k1,
+  // so that neighbours in a block are neighbours in memory (the table's rows
+  // are long enough to be read in any order).  In the order of n every access was a
+  // line of its own: d=1 nf=49152, 12 grids 15.2 -> 11.8 us, fp32 12.9 -> 9.3.
+  const int q = (int)blockIdx.x * PPB + lp;
+  const int L1 = (int)a.L1, L2 = (int)a.L2, nk1 = a.fourstep ? (int)a.M / L2 + 1 : 1;
+  const int k2 = a.fourstep ? q / nk1 : q, k1 = q - k2 * nk1;
+  const int n0 = a.fourstep ? k2 + L2 * k1 : q;
+  const bool act = lp < PPB && n0 <= (int)a.M && (!a.fourstep || k2 < L2);
   int64_t st0 = 0, st1 = 0;
   T D = T(0);
   if (act) {
-    int64_t nv[3] = {n0, 0, 0}, nvc[3] = {-n0, 0, 0};
-    st0 = radial_store(a, nv);
-    st1 = radial_store(a, nvc);
+    if (!a.fourstep) {
+      st0 = a.M + n0;
+      st1 = a.M - n0;
+    } else {  // -n is mode L1 L2 - n
+      st0 = (int64_t)k2 * L1 + k1;
+      st1 = n0 == 0 ? 0 : (k2 > 0 ? (int64_t)(L2 - k2) * L1 + (L1 - 1 - k1) : L1 - k1);
+    }
     D = dec[n0];
     const int g = j / 2;
     V z = V{T(0), T(0)}, zc = V{T(0), T(0)};
@@ -614,7 +625,7 @@ __global__ __launch_bounds__(kThreads) void mode_radial_1d_kernel(
   }
   __syncthreads();
   if (act) {
-    const T* Ar = Atab + n0 * NP;
+    const T* Ar = Atab + (int64_t)n0 * NP;
     V acc = V{T(0), T(0)};
 #pragma unroll 8
     for (int k = 0; k < NK; ++k) {
@@ -692,8 +703,9 @@ void launch_radial_nk(Plan* P) {
   }
   if (P->d == 1) {
     constexpr int PPB = kThreads / NK;
+    const int64_t np = a.fourstep ? a.L2 * (a.M / a.L2 + 1) : a.Q;
     for (int set = 0; set < a.nsets; ++set) {
-      hipLaunchKernelGGL((mode_radial_1d_kernel<T, NK>), dim3((unsigned)((a.Q + PPB - 1) / PPB)),
+      hipLaunchKernelGGL((mode_radial_1d_kernel<T, NK>), dim3((unsigned)((np + PPB - 1) / PPB)),
                          dim3(kThreads), 0, P->stream, a, C + set * a.set_stride,
                          P->atab.as<T>(), P->dec.as<T>());
       GP_CHECK_LAUNCH();
