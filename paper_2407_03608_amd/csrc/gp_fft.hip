@@ -7,7 +7,8 @@
 // window; everything else is zero), the last stage stores straight to HBM
 // (only the output window later steps read), and the stages in between
 // exchange data through LDS one real component at a time (a padded buffer of
-// L + L/32 reals per sequence).  Radices go up to 32 (24 for lengths 3*2^k):
+// L + L/32 reals per sequence; strided passes interleave the workgroup's
+// sequences, see kCols).  Radices go up to 32 (24 for lengths 3*2^k):
 // an 8192-point transform is three stages with 32 elements per thread
 // (32*32*8) and four with 16 (16*16*16*2); a 6144-point one with 24 elements
 // per thread is four (24*8*8*4).
