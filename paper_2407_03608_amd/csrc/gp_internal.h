@@ -172,6 +172,8 @@ struct Plan : PlanRules {
   } gv;
   DevBuf mA, mB, mB2, mC;     // batched grids for up to m_cap vectors (allocated on first use)
   int m_cap = 0;
+  DevBuf mpart;               // partial tiles of m_part vectors where lists are split (m_part = 1: rec.part)
+  int m_part = 1;
   DevBuf vec;                 // fp64 scratch vectors for matvec / CG (sorted order)
   // CG reductions (allocated once per plan): per-block partial sums, the
   // scalar slots of the solver and a pinned host mirror of those slots
@@ -239,7 +241,7 @@ void posterior_sorted(Plan* P, const double* x_sorted, int64_t m, const double* 
 // the grids of sum_i xs_i delta(x - x_i) over the points of R (sorted order)
 // through spreading, both FFTs and the mode mixing; interp_from_grid then
 // writes ys = K~(points of R', those points) xs for any record set R'.
-void forward_from(Plan* P, Records& R, const double* xs);
+void forward_from(Plan* P, const Records& R, const double* xs);
 void interp_from_grid(Plan* P, const Records& R, double* ys);
 // Kernel arguments of the spreading and interpolation kernels for one point
 // set (training points or targets) and one chunk of grid pairs.
@@ -272,9 +274,11 @@ inline bool spread_uses_sub_tiles(const Plan* P) { return spread_sub_side(P) > 0
 // Device bytes of the sub-tile lists (split: with the items and partial tiles of
 // long ones), bounded before the points are sorted.
 size_t spread_list_bound_bytes(const Plan* P, int64_t n, bool split);
+// Device bytes of one vector's partial tiles (0: no list is split).
+size_t spread_partial_bytes(const Plan* P, const Records& R);
 void build_spread_lists(Plan* P, Records& R);
 // xs: nsets consecutive vectors, into consecutive grid sets
-void spread_sub_launch(Plan* P, Records& R, const double* xs, int nsets);
+void spread_sub_launch(Plan* P, const Records& R, const double* xs, int nsets);
 // out[0..n) = exclusive prefix sums of the counts in[0..n) (device arrays, on
 // stream s); *total = their sum, read back to the host.
 void exclusive_scan_counts(const int* in, int64_t n, int64_t* out, hipStream_t s, int64_t* total);

@@ -704,7 +704,7 @@ void launch_interp(Plan* P, const Records& R, const double* xs, double* ys, int 
 // The points of R for nsets consecutive vectors (into the grid sets from the
 // current one on).
 template <typename T>
-void spread_dispatch(Plan* P, Records& R, const double* xs, int nsets = 1) {
+void spread_dispatch(Plan* P, const Records& R, const double* xs, int nsets = 1) {
   if (spread_uses_sub_tiles(P)) {  // one wavefront per sub-tile from the point set's lists
     spread_sub_launch(P, R, xs, nsets);
     return;
@@ -933,7 +933,7 @@ void fft_all(Plan* P, int sign) {
 }
 
 template <typename T>
-void forward_and_mix(Plan* P, Records& R, const double* xs) {
+void forward_and_mix(Plan* P, const Records& R, const double* xs) {
   spread_dispatch<T>(P, R, xs);
   fft_all(P, -1);
   mix_modes(P);
@@ -1001,8 +1001,15 @@ int multi_capacity(Plan* P, int want) {
   return (int)std::max<size_t>(1, std::min<size_t>((size_t)want, fit));
 }
 
+// Partial tiles of several vectors at once, at most: the vectors of a product
+// beyond them are spread in groups, so that split lists never need more memory than this
+// beside the grids (dense points on a small grid: 58 MB per vector against 20 MB of
+// grids) and a product runs without any of it.
+constexpr size_t kMultiPartBytes = (size_t)64 << 20;
+
 static void ensure_multi(Plan* P, int m) {
   if (m <= P->m_cap) return;
+  P->m_cap = 0;  // until every buffer is there
   const size_t cs = P->precision == GP_FP64 ? 16 : 8;
   const size_t G = (size_t)P->npair * m;
   P->mA.alloc(G * P->grid_elems[0] * cs, P->stream);
@@ -1011,6 +1018,16 @@ static void ensure_multi(Plan* P, int m) {
   P->mC.alloc(G * P->grid_elems[3] * cs, P->stream);
   // the 1-D four-step keeps zeros in A outside the active box (see fft_all)
   if (P->fourstep) GP_HIP(hipMemsetAsync(P->mA.p, 0, P->mA.bytes, P->stream));
+  const size_t one = spread_partial_bytes(P, P->rec);
+  const int k = one > 0 ? (int)std::min<size_t>(m, kMultiPartBytes / one) : 1;
+  if (k > P->m_part) {
+    P->m_part = 1;
+    try {
+      P->mpart.alloc(k * one, P->stream);
+      P->m_part = k;
+    } catch (const Error&) {  // one vector at a time through the plan's own
+    }
+  }
   P->m_cap = m;
 }
 
@@ -1095,7 +1112,7 @@ void posterior_sorted(Plan* P, const double* xs, int64_t m, const double* tpts,
 // Grids for the points of R weighted by xs (sorted order of R): spread,
 // forward FFT, mode mixing, inverse FFT.  interp_from_grid then evaluates the
 // result at the points of another record set of the same plan.
-void forward_from(Plan* P, Records& R, const double* xs) {
+void forward_from(Plan* P, const Records& R, const double* xs) {
   if (P->precision == GP_FP64)
     forward_and_mix<double>(P, R, xs);
   else

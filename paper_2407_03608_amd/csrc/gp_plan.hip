@@ -82,7 +82,7 @@ void retag_plan_stream(Plan* P, hipStream_t st) {
                     &R.in_work2, &R.part, &R.sub_off, &R.sub_list, &P->nodes_d, &P->bary_d,
                     &P->gtab, &P->etab, &P->vtd, &P->lr_off, &P->atab, &P->rowidx, &P->mode_tiles, &P->dec,
                     &P->tw[0], &P->tw[1], &P->tw[2], &P->tw4, &P->gridA, &P->gridB, &P->gridB2,
-                    &P->gridC, &P->mA, &P->mB, &P->mB2, &P->mC, &P->vec, &P->cg_part, &P->cg_S};
+                    &P->gridC, &P->mA, &P->mB, &P->mB2, &P->mC, &P->mpart, &P->vec, &P->cg_part, &P->cg_S};
   for (DevBuf* b : bufs)
     if (b->p) b->s = st;
 }

@@ -534,17 +534,16 @@ void exclusive_scan(const In* in, int64_t n, int64_t* out, hipStream_t s, int64_
 }
 
 template <typename T, int D>
-void launch_sub(Plan* P, Records& R, const double* xs, int nsets) {
+void launch_sub(Plan* P, const Records& R, const double* xs, int nsets) {
   using V = typename V2<T>::type;
   PhaseScope ps(P, PH_SPREAD);
   NuArgs a = nu_args(P, R);
   a.n_slots = (int)R.n_slots;
   int lg = 0;
   while ((1 << lg) < R.sub_st) ++lg;
-  // partial tiles of several vectors at once: grown on first use
-  const size_t cells = (size_t)1 << (D * lg);
-  const size_t need = (size_t)nsets * R.n_slots * P->npair * cells * sizeof(V);
-  if (R.n_slots > 0 && R.part.bytes < need) R.part.alloc(need, P->stream);
+  // where lists are split, as many vectors at once as there are partial tiles for
+  const int group = R.n_slots > 0 && nsets > 1 ? P->m_part : nsets;
+  V* part = group > 1 ? P->mpart.as<V>() : R.part.as<V>();
   // equal chunks of grid pairs, at most kGCmax each
   const int nch = (P->npair + kGCmax - 1) / kGCmax;
   const int gc = (P->npair + nch - 1) / nch;
@@ -571,10 +570,20 @@ void launch_sub(Plan* P, Records& R, const double* xs, int nsets) {
   const int win = D > 1 ? P->w + 2 * (R.sub_st - 1) : P->w;
   const size_t smem = ((size_t)kSpreadBatch * ((D * win) | 1) * sizeof(T) + 15) / 16 * 16;
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblk, nch, nsets), dim3(kSubThreads), smem, P->stream, a, lg,
-                       grp, (unsigned)ni, per, set_stride, xs, R.pw.as<T>(), R.rs, R.sub_off.as<int64_t>(),
-                       R.sub_list.as<int2>(), split ? R.sp_work.as<int4>() : nullptr, R.part.as<V>(), grid);
-    GP_CHECK_LAUNCH();
+    for (int set = 0; set < nsets; set += group) {
+      const unsigned ns = (unsigned)std::min(group, nsets - set);
+      V* gset = grid + set * set_stride;
+      hipLaunchKernelGGL(kern, dim3((unsigned)nblk, nch, ns), dim3(kSubThreads), smem, P->stream, a, lg,
+                         grp, (unsigned)ni, per, set_stride, xs + set * R.n, R.pw.as<T>(), R.rs,
+                         R.sub_off.as<int64_t>(), R.sub_list.as<int2>(),
+                         split ? R.sp_work.as<int4>() : nullptr, part, gset);
+      GP_CHECK_LAUNCH();
+      if (R.n_sp_red > 0) {
+        hipLaunchKernelGGL((spread_reduce_kernel<T, D>), dim3((unsigned)R.n_sp_red, 1, ns), dim3(256), 0,
+                           P->stream, a, lg, set_stride, R.sp_red.as<int4>(), part, gset);
+        GP_CHECK_LAUNCH();
+      }
+    }
   };
   // matrix instructions per 16 cells (fp32: 4 weights each) and loads of 16 window values
   const int nm = sizeof(T) == 8 ? 1 : (2 * gc + 3) / 4, kw = (D * P->w + 15) / 16;
@@ -601,11 +610,6 @@ void launch_sub(Plan* P, Records& R, const double* xs, int nsets) {
   }
 #undef GP_SUB_KW
 #undef GP_SUB_GO
-  if (R.n_sp_red > 0) {
-    hipLaunchKernelGGL((spread_reduce_kernel<T, D>), dim3((unsigned)R.n_sp_red, 1, nsets), dim3(256), 0,
-                       P->stream, a, lg, set_stride, R.sp_red.as<int4>(), R.part.as<V>(), grid);
-    GP_CHECK_LAUNCH();
-  }
 }
 
 template <int D, bool FILL>
@@ -657,6 +661,13 @@ size_t spread_list_bound_bytes(const Plan* P, int64_t n, bool split) {
   const size_t cs = P->precision == GP_FP64 ? 16 : 8;
   return (size_t)total * sizeof(int2) + (size_t)(2 * nsub + 1) * sizeof(int64_t) +
          (size_t)(items + slots) * sizeof(int4) + (size_t)slots * cells * P->npair * cs;
+}
+
+size_t spread_partial_bytes(const Plan* P, const Records& R) {
+  if (!spread_uses_sub_tiles(P)) return 0;
+  size_t cells = 1;
+  for (int r = 0; r < P->d; ++r) cells *= R.sub_st;
+  return (size_t)R.n_slots * cells * P->npair * (P->precision == GP_FP64 ? 16 : 8);
 }
 
 // The exact source lists of sub-tile spreading, built on the device from the
@@ -718,10 +729,8 @@ void build_spread_lists(Plan* P, Records& R) {
     R.n_sp_work = tot[0];
     R.n_slots = tot[1];
     R.n_sp_red = tot[2];
-    int64_t cells = 1;
-    for (int r = 0; r < P->d; ++r) cells *= st;
-    const size_t cs = P->precision == GP_FP64 ? 16 : 8;
-    R.part.alloc((size_t)R.n_slots * cells * P->npair * cs, s);
+    R.sub_st = st;
+    R.part.alloc(spread_partial_bytes(P, R), s);
     GP_HIP(hipStreamSynchronize(s));  // n3 and o3 are released on return
   }
   GP_HIP(hipStreamSynchronize(s));  // &total is a host stack value
@@ -734,7 +743,7 @@ void exclusive_scan_counts(const int* in, int64_t n, int64_t* out, hipStream_t s
   exclusive_scan<int>(in, n, out, s, total);
 }
 
-void spread_sub_launch(Plan* P, Records& R, const double* xs, int nsets) {
+void spread_sub_launch(Plan* P, const Records& R, const double* xs, int nsets) {
   if (R.n_sub <= 0) throw Error{GP_EDEVICE, "internal: sub-tile lists missing"};
   const bool f64 = P->precision == GP_FP64;
   if (P->d == 1) f64 ? launch_sub<double, 1>(P, R, xs, nsets) : launch_sub<float, 1>(P, R, xs, nsets);

@@ -211,6 +211,46 @@ def _fits_lean(gp, prob, info, kw):
     return b < info["device_bytes"]
 
 
+@pytest.mark.parametrize("d,n,M,n_sigma,m,prec", [
+    (2, 60000, 24, 13, 6, 0), (1, 30000, 60, 23, 3, 0), (2, 60000, 24, 13, 5, 1), (3, 40000, 8, 7, 4, 0),
+])
+def test_multi_split_lists_memory(gp, d, n, M, n_sigma, m, prec):
+    """Several vectors on a plan whose lists are split (most points in one cell):
+    the bits of single solves, and beside the grids and the solver's vectors at most
+    64 MB for partial tiles however many vectors there are; single products
+    before and after have the same bits."""
+    import torch
+    rng = np.random.default_rng(n)
+    prob = inputs.random_small(d, n, seed=d, nu=1.5, lmin=0.1, lmax=0.25, eta=1.0)
+    prob.x[: n - n // 4] = 0.37 + 1e-2 * rng.standard_normal((n - n // 4, d))
+    prob.x[0], prob.x[-1] = 0.0, 1.0
+    P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, 1e-4 if prec else 1e-8,
+                precision=prec, M=M, n_sigma=n_sigma)
+    info = P.info()
+    y = rng.standard_normal((m, n))
+    Y = cuda(y)
+    before = host(P.matvec(Y[0]))
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    X = host(P.cg_solve_multi(Y, tol=1e-14, max_iter=2)[0])
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    # grids A, B, B2, C are at most the transform's size each; the solver keeps
+    # five vectors per column and torch the result
+    cs = 8 if prec else 16
+    nf, na, mc = info["nf"][0], info["na"], 2 * info["M"] + 1
+    grids = {1: na[0] + 2 * mc, 2: na[0] * na[1] + (max(na) + 8) * (mc + 8) + mc ** 2,
+             3: na[0] * na[1] * na[2] + na[2] * na[1] * mc + na[2] * mc ** 2 + mc ** 3}[d]
+    if nf > 8192:
+        grids = 3 * nf
+    bound = m * (info["n_pairs"] * grids * cs + 6 * n * 8) + (64 << 20)
+    say(f"multi d={d} prec={prec} m={m}: {used / 2**20:.0f} MB used, {bound / 2**20:.0f} MB allowed")
+    assert used <= bound + (32 << 20), (used, bound)  # the pool takes whole blocks
+    for j in range(m):
+        assert np.array_equal(X[j], host(P.cg_solve(Y[j], tol=1e-14, max_iter=2)[0])), j
+    assert np.array_equal(before, host(P.matvec(Y[0])))
+
+
 @pytest.mark.parametrize("d,n,m,prec", [(1, 300, 1, 0), (2, 3000, 5000, 0), (2, 900, 40, 1), (3, 500, 300, 0)])
 def test_posterior_mean_streams(gp, d, n, m, prec):
     """The targets are read on a stream beside the plan's: they may be written by
