@@ -177,7 +177,7 @@ struct Plan : PlanRules {
   DevBuf vec;                 // fp64 scratch vectors for matvec / CG (sorted order)
   // CG reductions (allocated once per plan): per-block partial sums, the
   // scalar slots of the solver and a pinned host mirror of those slots
-  DevBuf cg_part;             // double [kCgPart]
+  DevBuf cg_part;             // double [kCgBlocks + min(kCgBlocks, ceil(n / 256))]
   DevBuf cg_S;                // double [kCgScalars]
   double* cg_hS = nullptr;    // pinned host, kCgScalars
   size_t device_bytes = 0;

@@ -659,6 +659,9 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
     }
     return (size_t)G * (szA + szB + szB2 + szC) * cs;
   };
+  // (the three values per row beyond the window and the weights are not held: they
+  // cover the second set of partial sums below, so that a limit admits what it did
+  // when rows were padded and CG kept one set)
   size_t bytes = 0;
   bytes += (size_t)n * (sizeof(int) * (1 + d) + ts * (d * P->w + P->nk + 1 + 3));
   bytes += (size_t)(P->n_bins + 1) * sizeof(int);
@@ -669,7 +672,7 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
              (d == 2 ? (size_t)(P->M / kModeTileX + 1) * (P->M / kModeTileY + 1) * sizeof(int) : 0);
   else
     bytes += (size_t)P->nt_eff * P->nk * (P->M + 1) * ts * 2;
-  bytes += (size_t)n * 8 * sizeof(double) + (kCgPart + kCgScalars) * sizeof(double);  // vectors
+  bytes += (size_t)n * 8 * sizeof(double) + (kCgBlocks + kCgScalars) * sizeof(double);  // vectors
   bytes += (size_t)nf * cs * 2;
   // The sub-tile lists of the spreading; where a byte limit leaves no room for
   // them, tiles without lists (fp32 in d >= 2: lists that are not split)
@@ -827,7 +830,8 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
   P->gv.nsets = 1;
   P->gv.cur = 0;
   P->vec.alloc((size_t)n * 8 * sizeof(double), P->stream);
-  P->cg_part.alloc(kCgPart * sizeof(double), P->stream);
+  // the second set is used up to one sum per 256 points
+  P->cg_part.alloc((kCgBlocks + std::min<int64_t>(kCgBlocks, (n + 255) / 256)) * sizeof(double), P->stream);
   P->cg_S.alloc(kCgScalars * sizeof(double), P->stream);
   P->cg_hS = pinned_scalars_get();
   GP_HIP(hipStreamSynchronize(s));

@@ -251,6 +251,45 @@ def test_multi_split_lists_memory(gp, d, n, M, n_sigma, m, prec):
     assert np.array_equal(before, host(P.matvec(Y[0])))
 
 
+@pytest.mark.parametrize("d,n,M,tol,prec,dw,n_sigma,nbytes", [
+    # nbytes: what a plan without lists, column blocks and padded rows has always counted
+    (1, 2, 20, 1e-08, 0, 0.25, 5, 24528),
+    (1, 300, 60, 1e-08, 0, 0.25, 7, 166728),
+    (1, 70000, 6200, 1e-08, 0, 0.25, 5, 22915152),
+    (1, 5000, 60, 0.0001, 1, 0.25, 5, 697788),
+    (2, 2, 3, 0.0001, 0, 0.25, 3, 65772),
+    (2, 500, 40, 1e-08, 0, 0.25, 7, 1873576),
+    (2, 70000, 130, 1e-06, 0, 0.25, 5, 32328992),
+    (2, 500, 41, 0.0001, 1, 0.25, 4, 749500),
+    (2, 300, 5, 0.001, 1, 0.45, 3, 400576),
+    (2, 300, 3, 0.0001, 1, 0.45, 3, 739596),
+    (2, 300, 2, 0.01, 1, 0.45, 3, 261988),
+    (2, 300, 6, 1e-05, 1, 0.4, 3, 284880),
+    (2, 70000, 100, 0.0001, 1, 0.25, 5, 17676816),
+    (3, 2, 4, 0.0001, 0, 0.25, 3, 736500),
+    (3, 2000, 12, 1e-06, 0, 0.25, 5, 13639672),
+    (3, 70000, 66, 1e-06, 0, 0.25, 5, 1130798784),
+    (3, 2000, 12, 0.0001, 1, 0.25, 5, 7017752),
+    (3, 300, 3, 0.0001, 1, 0.45, 3, 15828404),
+    (3, 300, 2, 0.001, 1, 0.45, 3, 15489120),
+    (3, 300, 5, 1e-05, 1, 0.45, 3, 37753460),
+    (3, 70000, 64, 0.0001, 1, 0.25, 5, 559441452),
+])
+def test_byte_limit_admits_plans_without_lists(gp, d, n, M, tol, prec, dw, n_sigma, nbytes):
+    """max_device_bytes admits every plan whose form without spreading lists fits."""
+    prob = inputs.random_small(d, n, seed=d, nu=1.5, lmin=0.1, lmax=0.25)
+    arg = [cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, tol]
+    kw = dict(precision=prec, M=M, dw=dw, n_sigma=n_sigma)
+    assert gp.plan_query(*arg, max_device_bytes=1, **kw) == nbytes
+    least = min(nbytes, gp.plan_query(*arg, **kw))  # few points: the form with lists may be the smaller one
+    a = cuda(np.random.default_rng(2).standard_normal(n))
+    got = host(gp.Plan(*arg, max_device_bytes=nbytes, **kw).matvec(a))
+    ref = host(gp.Plan(*arg, **kw).matvec(a))
+    assert max_rel(got, ref) <= (ORDER_FP32 if prec else ORDER_FP64)
+    with pytest.raises(gp.GpError):
+        gp.Plan(*arg, max_device_bytes=least - 1, **kw)
+
+
 @pytest.mark.parametrize("d,n,m,prec", [(1, 300, 1, 0), (2, 3000, 5000, 0), (2, 900, 40, 1), (3, 500, 300, 0)])
 def test_posterior_mean_streams(gp, d, n, m, prec):
     """The targets are read on a stream beside the plan's: they may be written by
