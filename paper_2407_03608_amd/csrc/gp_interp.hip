@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "gp_internal.h"
+#include "gp_window.h"
 
 namespace gp {
 namespace {
@@ -63,7 +64,8 @@ struct TileShape {
   static constexpr size_t smem = main_bytes + (size_t)(3 * NP + BK + 8) * sizeof(int);
 };
 
-template <typename T, int D, int W, int C0, int C1, int C2, int RG, int NT>
+// The order of a point's sum and its measured error: window_sum (ROWS: see interp_w).
+template <typename T, int D, int W, int C0, int C1, int C2, int RG, int NT, bool ROWS>
 __global__ __launch_bounds__(NT) void interp_tile_kernel(
     NuArgs a, const typename V2<T>::type* __restrict__ grid, int64_t set_stride,
     const int* __restrict__ cell, const T* __restrict__ pw, int rs,
@@ -211,39 +213,9 @@ __global__ __launch_bounds__(NT) void interp_tile_kernel(
       }
       __syncthreads();
       if (act) {
-        T sx = 0, sy = 0;
-#pragma unroll
-        for (int j = 0; j < HP; ++j) {
-          const V* tp = tr0 + (j + 1 < HP ? RG * j * HS : lastoff);
-          if constexpr (D > 2) {
-            T ax = 0, ay = 0;
-#pragma unroll
-            for (int q1 = 0; q1 < W; ++q1) {
-              T rx = 0, ry = 0;
-#pragma unroll
-              for (int q0 = 0; q0 < W; ++q0) {
-                const V gv = tp[q1 * S::PS0 + q0];
-                rx += p0[q0] * gv.x;
-                ry += p0[q0] * gv.y;
-              }
-              ax += p1[q1] * rx;
-              ay += p1[q1] * ry;
-            }
-            sx += p2[j] * ax;
-            sy += p2[j] * ay;
-          } else {
-            T rx = 0, ry = 0;
-#pragma unroll
-            for (int q0 = 0; q0 < W; ++q0) {
-              const V gv = tp[q0];
-              rx += p0[q0] * gv.x;
-              ry += p0[q0] * gv.y;
-            }
-            sx += p1[j] * rx;
-            sy += p1[j] * ry;
-          }
-        }
-        part += (double)wa * (double)sx + (double)wb * (double)sy;
+        double bx, by;
+        window_sum<T, V, D, W, HP, RG, S::PS0, HS, ROWS>(tr0, lastoff, p0, p1, p2, &bx, &by);
+        part += (double)wa * bx + (double)wb * by;
       }
       if (g + 1 < a.npair) {
         wa = wrow[2 * g + 2];
@@ -321,7 +293,7 @@ __global__ __launch_bounds__(kWaveThreads) void interp_wave_kernel(
   } else {
     for (int g = 0; g < a.npair; ++g) {
       const V* gp = grid + (int64_t)g * a.pair_stride + base;
-      T sx = 0, sy = 0;
+      double sx = 0, sy = 0;  // up to 64 rows: fp32 grids' in fp64
 #pragma unroll NU
       for (int j = 0; j < NS; ++j) {
         const int row = ly + YL * j, rc = min(row, ROWS - 1);
@@ -330,10 +302,10 @@ __global__ __launch_bounds__(kWaveThreads) void interp_wave_kernel(
         T wv = pr[W + q1];
         if (D > 2) wv *= pr[2 * W + q2];
         wv = row < ROWS ? wv * p0 : T(0);
-        sx += wv * v.x;
-        sy += wv * v.y;
+        sx += (double)wv * (double)v.x;
+        sy += (double)wv * (double)v.y;
       }
-      part += (double)pr[D * W + 2 * g] * (double)sx + (double)pr[D * W + 2 * g + 1] * (double)sy;
+      part += (double)pr[D * W + 2 * g] * sx + (double)pr[D * W + 2 * g + 1] * sy;
     }
   }
 #pragma unroll
@@ -362,14 +334,14 @@ struct InterpCall {
   int64_t set_stride;
 };
 
-template <typename T, int D, int W, int C0, int C1, int C2, int RG, int NT>
+template <typename T, int D, int W, int C0, int C1, int C2, int RG, int NT, bool ROWS = false>
 void launch_tile(const InterpCall& c, bool per_bin) {
   using S = TileShape<T, D, W, C0, C1, C2, RG, NT>;
   static_assert(S::smem <= 80 * 1024, "at least two workgroups per CU");
   const Records& R = *c.R;
   const int64_t nw = per_bin ? R.n_in_work : R.n_in_work2;
   if (nw == 0) return;
-  auto kern = interp_tile_kernel<T, D, W, C0, C1, C2, RG, NT>;
+  auto kern = interp_tile_kernel<T, D, W, C0, C1, C2, RG, NT, ROWS>;
   if (S::smem > 64 * 1024) allow_lds(reinterpret_cast<const void*>(kern), S::smem);
   NuArgs a = nu_args(c.P, R);
   a.add_noise = c.add_noise;
@@ -431,13 +403,21 @@ void interp_w(const InterpCall& c) {
         // from one window's worth of points per block on (fp32 w=5, staged against waves:
         // 1.06 windows 0.34 / 0.40 ms, 1.7 0.37 / 0.60, 3.2 0.40 / 0.99)
         if ((double)c.R->n * W * W * W > blocks * S::NC) {
+          // fp32, w = 7: rows of 26 weights on took a block of 2x2x1 bins over the LDS that
+          // the former kernel had, and the per-bin one joins rows in fp64
+          if constexpr (sizeof(T) == 4 && W == 7) {
+            if (P->nkp >= 26) {
+              launch_tile<T, 3, W, 16, 16, 8, 1, 512, true>(c, false);
+              return;
+            }
+          }
           launch_tile<T, 3, W, 16, 16, 8, 1, 512>(c, false);
           return;
         }
       } else if constexpr (kTile3Bin<T, D, W>) {
         using S = TileShape<T, 3, W, 8, 8, 8, 1, 256>;
         if ((double)c.R->n * W * W * W > 2.0 * (double)P->n_bins * S::NC) {
-          launch_tile<T, 3, W, 8, 8, 8, 1, 256>(c, true);
+          launch_tile<T, 3, W, 8, 8, 8, 1, 256, (W > 7)>(c, true);
           return;
         }
       }

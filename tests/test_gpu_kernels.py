@@ -63,6 +63,30 @@ def test_interp_default_matches_per_bin(gp, d, n, M, tol, prec):
         assert e <= (ORDER_FP32 if prec else ORDER_FP64), e
 
 
+@pytest.mark.parametrize("d,M,tol,n_sigma,upsample", [
+    (2, 40, 1e-3, 0, 0), (2, 40, 1e-4, 0, 0), (2, 40, 1e-6, 0, 1.25), (2, 40, 1e-4, 9, 0),
+    (3, 10, 1e-6, 27, 0), (3, 10, 1e-6, 0, 1.5), (3, 10, 1e-6, 5, 1.5),
+])
+def test_interp_fp32_joins_rows_in_fp64(gp, d, M, tol, n_sigma, upsample):
+    """Staged interpolation of fp32 grids in 2-D, and in 3-D from w = 8 on (w = 7: rows
+    of 26 weights on), against the per-bin kernel: both add a window row in fp32, in
+    order, and the rows in fp64.  2-D: the same to fp64 rounding.  3-D: the per-bin
+    kernel rounds the product of a row's two window values to fp32, an error of at
+    most 2^-24 / sqrt(12) of each row's share, of rows of one sign."""
+    n = 40000
+    prob = inputs.random_small(d, n, seed=3, nu=0.5, lmin=0.1, lmax=0.25, constant_scales=n_sigma == 0)
+    kw = dict(tol=tol, nufft_tol=tol, precision=1, M=M, dw=0.25, n_sigma=n_sigma)
+    if upsample:
+        kw["upsample"] = upsample
+    a = np.random.default_rng(1).standard_normal(n)
+    got, info = _matvec(gp, prob, a, **kw)
+    ref, _ = _matvec(gp, prob, a, interp=2, **kw)
+    e = np.sqrt(np.mean((got - ref) ** 2) / np.mean(ref ** 2)) * 2 ** 24
+    say(f"fp32 rows d={d} w={info['w']} nk={n_sigma + 1}: {e:.4f} of 2^-24")
+    assert d == 2 or info["w"] >= 7
+    assert e <= (1e-6 if d == 2 else 2 / np.sqrt(12)), e
+
+
 @pytest.mark.parametrize("n,M,tol,prec", [
     (150, 4200, 1e-8, 0), (150, 6200, 1e-8, 0), (90, 15000, 1e-8, 0), (60, 50000, 1e-8, 0),
     (150, 4200, 1e-4, 1), (90, 33000, 1e-4, 1),

@@ -1,6 +1,6 @@
 """Host code under AddressSanitizer and UndefinedBehaviorSanitizer.
 
-Two host-only programs are compiled with g++ and run:
+Host-only programs are compiled with g++ and run:
 
 * the plan rules (``csrc/gp_rules.cpp``: parameter choice of section 3.5, the
   host tables, the step-3 row map and its low-rank factors of rem:step3, input
@@ -8,7 +8,9 @@ Two host-only programs are compiled with g++ and run:
   d, nu, tol, length ranges, precisions and oversampling factors, with the
   geometric invariants the kernels rely on checked for every plan;
 * the oracle (``oracle/oracle.cpp``) driven by ``tests/sanitize/oracle_main.cpp``,
-  which cross-checks its independent forms on small inputs.
+  which cross-checks its independent forms on small inputs;
+* the window sum of the staged interpolation (``csrc/gp_window.h``), whose error
+  on fp32 grids is measured against fp64 by ``tests/sanitize/window_main.cpp``.
 
 Any sanitizer report aborts the program (``-fno-sanitize-recover=all``).
 """
@@ -51,3 +53,11 @@ def test_oracle_under_sanitizers(tmp_path):
     out = _build_and_run(tmp_path, "oracle_san", ["tests/sanitize/oracle_main.cpp"],
                          extra=["-fopenmp"], env_extra={"OMP_NUM_THREADS": "2"})
     assert " 0 failures" in out, out
+
+
+def test_window_sum_error(tmp_path):
+    """fp32 window sums err no more, at any width, than quarters of the window's rows
+    added in fp32 and joined in fp64 (rows joined one by one where ROWS asks)."""
+    out = _build_and_run(tmp_path, "window", ["tests/sanitize/window_main.cpp"],
+                         extra=["-O2", "-mfma", "-ffp-contract=fast"])
+    assert out.rstrip().endswith("\n0 failures"), out
