@@ -73,9 +73,6 @@ Plan::~Plan() {
     (void)hipEventDestroy(ev.b);
   }
   for (auto e : pool) (void)hipEventDestroy(e);
-  if (side_in) (void)hipEventDestroy(side_in);
-  if (side_out) (void)hipEventDestroy(side_out);
-  if (side) (void)hipStreamDestroy(side);
 }
 
 // Iterative refinement in the caller's point order (the two plans may sort the

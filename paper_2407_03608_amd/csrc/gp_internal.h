@@ -189,10 +189,7 @@ struct Plan : PlanRules {
   };
   std::vector<Ev> events;
   std::vector<hipEvent_t> pool;
-  // posterior mean: the targets' records are built here while the forward pass
-  // runs on the plan's stream (created at the first call)
-  hipStream_t side = nullptr;
-  hipEvent_t side_in = nullptr, side_out = nullptr;
+  bool predicted = false;     // a posterior mean has been asked of this plan
   ~Plan();
 };
 

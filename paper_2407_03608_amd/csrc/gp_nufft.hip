@@ -23,6 +23,7 @@
 #include <mutex>
 
 #include "gp_internal.h"
+#include "gp_pool.h"
 
 namespace gp {
 
@@ -1056,11 +1057,67 @@ void matvec_multi_sorted(Plan* P, int m, const double* xs, double* ys, int add_n
   P->gv = own;
 }
 
+namespace {
+// A stream beside a plan's and the events that order the two, leased for one call
+// from those that the process keeps idle (at most kIdleSides; calls in flight beyond
+// them make and destroy their own).
+struct Side {
+  hipStream_t s = nullptr;
+  hipEvent_t in = nullptr, out = nullptr;
+};
+constexpr size_t kIdleSides = 4;
+
+class SideLease {
+ public:
+  // make: create one where none is idle
+  SideLease(int device, bool make) : device_(device) {
+    if (pool().take(device, &side_)) {
+      held_ = true;
+    } else if (make) {
+      held_ = true;
+      try {
+        GP_HIP(hipStreamCreateWithFlags(&side_.s, hipStreamNonBlocking));
+        GP_HIP(hipEventCreateWithFlags(&side_.in, hipEventDisableTiming));
+        GP_HIP(hipEventCreateWithFlags(&side_.out, hipEventDisableTiming));
+      } catch (...) {
+        destroy();
+        throw;
+      }
+    }
+  }
+  ~SideLease() {
+    if (held_ && !(idle_ && pool().put(device_, side_))) destroy();
+  }
+  SideLease(const SideLease&) = delete;
+  SideLease& operator=(const SideLease&) = delete;
+  const Side* get() const { return held_ ? &side_ : nullptr; }
+  void release_idle() { idle_ = true; }  // nothing is queued on it any more
+
+ private:
+  static IdlePool<Side>& pool() {
+    static IdlePool<Side>* p = new IdlePool<Side>(kIdleSides);  // the streams last as long as the process
+    return *p;
+  }
+  void destroy() {
+    if (side_.out) (void)hipEventDestroy(side_.out);
+    if (side_.in) (void)hipEventDestroy(side_.in);
+    if (side_.s) (void)hipStreamDestroy(side_.s);
+    held_ = false;
+  }
+  int device_;
+  Side side_;
+  bool held_ = false, idle_ = false;
+};
+}  // namespace
+
 // Checking and sorting the targets is host work with several round trips, about as
 // long as the forward pass of a mid-sized plan, and needs nothing of it: the
-// pass is queued first and the records are built on a stream of their own (d=2
-// N=1e5, 5e4 targets: 1.36 -> 0.88 ms; N=500, 10 targets 0.46 -> 0.38).  A stream under capture keeps one stream, so
-// such a call fails at its first copy.
+// pass is queued first and the records are built on a stream beside the plan's (d=2
+// N=1e5, 5e4 targets: 1.36 -> 0.88 ms; N=500, 10 targets 0.46 -> 0.38).  Creating
+// that stream takes 3.2 ms where it is the second of the process and 0.06 later, and
+// a call saves 0.4, so a plan that has not predicted yet does not create one:
+// without an idle one its first call queues everything on the plan's stream.
+// Captured calls are refused: the targets cannot be checked on the host then.
 void posterior_sorted(Plan* P, const double* xs, int64_t m, const double* tpts,
                       const double* tsig, const double* tl, double* mu,
                       const std::function<void()>& check) {
@@ -1071,26 +1128,32 @@ void posterior_sorted(Plan* P, const double* xs, int64_t m, const double* tpts,
     check();
     throw Error{GP_EDEVICE, "the posterior mean cannot be captured"};
   }
-  if (!P->side) GP_HIP(hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking));
-  if (!P->side_in) GP_HIP(hipEventCreateWithFlags(&P->side_in, hipEventDisableTiming));
-  if (!P->side_out) GP_HIP(hipEventCreateWithFlags(&P->side_out, hipEventDisableTiming));
-  GP_HIP(hipEventRecord(P->side_in, main));  // the targets are ready where the caller's work is
-  GP_HIP(hipStreamWaitEvent(P->side, P->side_in, 0));
+  int dev = 0;
+  GP_HIP(hipGetDevice(&dev));
+  SideLease lease(P->device, P->predicted && dev == P->device);
+  const Side* side = lease.get();
+  P->predicted = true;
   Records T;
   DevBuf tmp;
   try {
+    if (side) {  // the targets are ready where the caller's work is
+      GP_HIP(hipEventRecord(side->in, main));
+      GP_HIP(hipStreamWaitEvent(side->s, side->in, 0));
+    }
     if (P->precision == GP_FP64)
       forward_and_mix<double>(P, P->rec, xs);
     else
       forward_and_mix<float>(P, P->rec, xs);
-    P->stream = P->side;
+    if (side) P->stream = side->s;
     check();
     int oob = 0;
     build_records_into(P, m, tpts, tsig, tl, T, &oob);
     if (oob) throw Error{GP_ERANGE, "posterior target outside the plan's box"};
     P->stream = main;
-    GP_HIP(hipEventRecord(P->side_out, P->side));
-    GP_HIP(hipStreamWaitEvent(main, P->side_out, 0));
+    if (side) {
+      GP_HIP(hipEventRecord(side->out, side->s));
+      GP_HIP(hipStreamWaitEvent(main, side->out, 0));
+    }
     tmp.alloc(m * sizeof(double), main);
     if (P->precision == GP_FP64)
       interp_dispatch<double>(P, T, nullptr, tmp.as<double>(), 0);
@@ -1100,11 +1163,12 @@ void posterior_sorted(Plan* P, const double* xs, int64_t m, const double* tpts,
                        m, T.perm.as<int>(), tmp.as<double>(), mu);
     GP_CHECK_LAUNCH();
     GP_HIP(hipStreamSynchronize(main));
+    lease.release_idle();
   } catch (...) {
     // nothing queued here outlives the call or the buffers of T
     P->stream = main;
-    (void)hipStreamSynchronize(P->side);
-    (void)hipStreamSynchronize(main);
+    const bool idle = !side || hipStreamSynchronize(side->s) == hipSuccess;
+    if (hipStreamSynchronize(main) == hipSuccess && idle) lease.release_idle();
     throw;
   }
 }

@@ -345,3 +345,46 @@ def test_posterior_mean_streams(gp, d, n, m, prec):
             bad[m // 2, 0] = 7.0
             with pytest.raises(gp.GpError):
                 P.posterior_mean(al, bad, *true[1:])
+
+
+def test_posterior_mean_plans_and_threads(gp):
+    """The first prediction of a plan, later ones and those of several plans in as many
+    threads (more than streams are kept idle): the same bits, refused calls between them."""
+    import threading
+
+    import torch
+    prob = inputs.random_small(2, 4000, seed=8, nu=1.5, lmin=0.1, lmax=0.25)
+    rng = np.random.default_rng(9)
+    al = cuda(rng.standard_normal(4000))
+    i = rng.integers(0, 4000, 700)
+    t = [cuda(v[i]) for v in (prob.x, prob.sigma, prob.l)]
+    bad = [t[0] + 3.0, t[1], t[2]]
+    torch.cuda.synchronize()
+
+    def plan(stream):
+        return gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, 1e-6, M=60, stream=stream)
+
+    want = host(plan(torch.cuda.Stream()).posterior_mean(al, *t))
+    out, err = [[] for _ in range(6)], []
+
+    def work(k):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                P = plan(s)
+                for r in range(4):
+                    out[k].append(host(P.posterior_mean(al, *t)))
+                    if (k + r) % 3 == 0:
+                        with pytest.raises(gp.GpError):
+                            P.posterior_mean(al, *bad)
+        except BaseException as e:  # noqa: BLE001
+            err.append(e)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+    for th in ts:
+        th.start()
+    for th in ts:
+        th.join()
+    assert not err, err
+    for o in out:
+        assert len(o) == 4 and all(np.array_equal(v, want) for v in o)

@@ -10,7 +10,8 @@ Host-only programs are compiled with g++ and run:
 * the oracle (``oracle/oracle.cpp``) driven by ``tests/sanitize/oracle_main.cpp``,
   which cross-checks its independent forms on small inputs;
 * the window sum of the staged interpolation (``csrc/gp_window.h``), whose error
-  on fp32 grids is measured against fp64 by ``tests/sanitize/window_main.cpp``.
+  on fp32 grids is measured against fp64 by ``tests/sanitize/window_main.cpp``;
+* the pool of idle resources (``csrc/gp_pool.h``), under ThreadSanitizer.
 
 Any sanitizer report aborts the program (``-fno-sanitize-recover=all``).
 """
@@ -24,11 +25,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SAN = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer"]
 
 
-def _build_and_run(tmp_path, name, sources, extra=(), env_extra=None):
+def _build_and_run(tmp_path, name, sources, extra=(), env_extra=None, san=SAN):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     exe = str(tmp_path / name)
-    cmd = ["g++", "-std=c++17", "-O1", "-g", *SAN, *extra, "-o", exe,
+    cmd = ["g++", "-std=c++17", "-O1", "-g", *san, *extra, "-o", exe,
            *[os.path.join(ROOT, s) for s in sources]]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
@@ -61,3 +62,9 @@ def test_window_sum_error(tmp_path):
     out = _build_and_run(tmp_path, "window", ["tests/sanitize/window_main.cpp"],
                          extra=["-O2", "-mfma", "-ffp-contract=fast"])
     assert out.rstrip().endswith("\n0 failures"), out
+
+
+def test_idle_pool_threads(tmp_path):
+    out = _build_and_run(tmp_path, "pool", ["tests/sanitize/pool_main.cpp"], extra=["-pthread", "-Wall"],
+                         san=["-fsanitize=thread", "-fno-sanitize-recover=all"])
+    assert out.rstrip().endswith("0 failures"), out
