@@ -386,23 +386,36 @@ void interp_w(const InterpCall& c) {
     bool fits = (double)P->na[0] * P->na[1] * P->na[2] * 2 * sizeof(T) < 4.0e9;  // 32-bit cell offsets
     for (int r = 0; r < D; ++r) fits = fits && P->tile[r] == def;
     // The block is staged for all of its points, a point's own window costs w^d
-    // cells and about as much again in partial lines: staging pays from two
-    // windows' worth of points per block on (d=3 N=2e5 fp64: windows fill 0.9 of
-    // a block, 0.82 ms by waves; d=2 N=1e5 fp64: 7 of a block, 0.10 ms staged)
+    // cells and about as much again in partial lines: staging pays from `line` windows'
+    // worth of points per block on (ms staged / by waves at the windows per block):
+    //  2-D, 2: d=2 N=1e5 fp64 at 7 0.10 staged
+    //  3-D, 2x2x1 bins, 1: fp32 w=5 1.06 0.34 / 0.40, 1.7 0.37 / 0.60, 3.2 0.40 / 0.99
+    //  3-D, one bin, 2: fp64 w=7 1.2 0.29 / 0.18, 2.4 0.30 / 0.30, 5 0.32 / 0.57; w=4 0.6
+    //  0.068 / 0.042, 2 0.075 / 0.102; w=8 3.1 0.49 / 0.42, 6.5 0.52 / 0.78; fp32 w=9 1.8 0.15 / 0.10,
+    //  3.7 0.16 / 0.20.  fp64 w=9 (8) and 10 (11), where staging takes six times as long
+    //  as at w=8 (why was not found): w=9 3.4 2.83 / 1.33, 7.2 2.9 / 2.7, 29 3.9 / 10.7; w=10 4.2
+    //  4.4 / 1.8, 8.7 4.5 / 3.8, 12 4.6 / 5.3.  fp64 from w=11 on fits no block; waves take 0.06 to 0.54 of the
+    //  per-bin kernel's time (interp = 2) from 3 to 60 points per bin (w=11, 12).
+    // The average is over all blocks.  Clustered points fill few of them: there the
+    // blocks that are staged count, at a line of twice (2-D: 1.5 times) as many windows, so that
+    // the empty border of uniform points does not change their kernel, and from one
+    // block per CU on (d=2 fp32 N=1e5 in one cluster 0.034 -> 0.016 ms, d=3 fp32 N=1e6 in
+    // eight 0.56 -> 0.25; with 80 blocks, d=2 fp64 N=1e4, 0.016 staged and 0.011 by waves).
+    auto dense = [&](double window, int nc, double blocks, int64_t staged, double line) {
+      const double cells = (double)c.R->n * window;
+      return cells > line * blocks * nc ||
+             (staged >= 256 && cells > line * (D == 2 ? 1.5 : 2.0) * (double)staged * nc);
+    };
     if (fits) {
       if constexpr (D == 2) {
         using S = TileShape<T, 2, W, 32, 32, 1, 2, 256>;
-        const double blocks = 0.25 * P->nbins[0] * P->nbins[1];
-        if ((double)c.R->n * W * W > 2.0 * blocks * S::NC) {
+        if (dense(W * W, S::NC, 0.25 * P->nbins[0] * P->nbins[1], c.R->n_in_work2, 2.0)) {
           launch_tile<T, 2, W, 32, 32, 1, 2, 256>(c, false);
           return;
         }
       } else if constexpr (kTile3Super<T, D, W>) {
         using S = TileShape<T, 3, W, 16, 16, 8, 1, 512>;
-        const double blocks = 0.25 * P->n_bins;
-        // from one window's worth of points per block on (fp32 w=5, staged against waves:
-        // 1.06 windows 0.34 / 0.40 ms, 1.7 0.37 / 0.60, 3.2 0.40 / 0.99)
-        if ((double)c.R->n * W * W * W > blocks * S::NC) {
+        if (dense(W * W * W, S::NC, 0.25 * P->n_bins, c.R->n_in_work2, 1.0)) {
           // fp32, w = 7: rows of 26 weights on took a block of 2x2x1 bins over the LDS that
           // the former kernel had, and the per-bin one joins rows in fp64
           if constexpr (sizeof(T) == 4 && W == 7) {
@@ -416,7 +429,8 @@ void interp_w(const InterpCall& c) {
         }
       } else if constexpr (kTile3Bin<T, D, W>) {
         using S = TileShape<T, 3, W, 8, 8, 8, 1, 256>;
-        if ((double)c.R->n * W * W * W > 2.0 * (double)P->n_bins * S::NC) {
+        constexpr double line = sizeof(T) == 4 || W < 9 ? 2.0 : (W == 9 ? 8.0 : 11.0);
+        if (dense(W * W * W, S::NC, (double)P->n_bins, c.R->n_in_work, line)) {
           launch_tile<T, 3, W, 8, 8, 8, 1, 256, (W > 7)>(c, true);
           return;
         }

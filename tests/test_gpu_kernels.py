@@ -87,6 +87,46 @@ def test_interp_fp32_joins_rows_in_fp64(gp, d, M, tol, n_sigma, upsample):
     assert e <= (1e-6 if d == 2 else 2 / np.sqrt(12)), e
 
 
+@pytest.mark.parametrize("n,M,staged", [(100000, 300, True), (60000, 100, True), (300, 300, False)])
+def test_interp_rule_counts_blocks_with_points(gp, n, M, staged):
+    """Points in one cluster of a large grid: the staged kernel where its blocks, those
+    that hold points, are full (fp32 in 2-D: then the rows are joined as the per-bin kernel
+    joins them, to fp64 rounding), lane groups where they are few."""
+    prob = inputs.random_small(2, n, seed=4, nu=0.5, lmin=0.1, lmax=0.25, constant_scales=True)
+    rng = np.random.default_rng(n)
+    prob.x[:] = np.clip(0.4 + 0.01 * rng.standard_normal((n, 2)), 0, 1)
+    prob.x[0], prob.x[-1] = 0.0, 1.0
+    kw = dict(tol=1e-4, precision=1, M=M, dw=0.25)
+    a = rng.standard_normal(n)
+    got, info = _matvec(gp, prob, a, **kw)
+    ref, _ = _matvec(gp, prob, a, interp=2, **kw)
+    e = np.sqrt(np.mean((got - ref) ** 2) / np.mean(ref ** 2)) * 2 ** 24
+    say(f"clustered n={n} M={M} na={info['na']}: {e:.4f} of 2^-24")
+    assert e <= 1e-6 if staged else 1e-3 < e <= 4, e
+
+
+@pytest.mark.parametrize("tol,n", [(1e-8, 120000), (1e-9, 120000), (1e-9, 500), (1e-8, 1000000), (1e-9, 1000000)])
+def test_interp_wide_windows_3d(gp, tol, n):
+    """fp64 in 3-D at w = 9 and 10 below and above the density at which blocks are
+    staged: the per-bin kernel's values, in clearly less than its time."""
+    prob = inputs.random_small(3, n, seed=6, nu=2.5, lmin=0.3, lmax=0.5)
+    a = np.random.default_rng(1).standard_normal(n)
+    out, ms = [], []
+    for interp in (0, 2):
+        P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, tol, M=60, dw=0.25, interp=interp)
+        v = cuda(a)
+        out.append(host(P.matvec(v)))
+        P.set_timing(True)
+        for _ in range(3):
+            P.matvec(v)
+        ms.append(P.timing()["interp"][1] / 3)
+        P.set_timing(False)
+    say(f"3-D w={P.info()['w']} n={n}: {ms[0]:.3f} ms, per-bin kernel {ms[1]:.3f}")
+    assert max_rel(out[0], out[1]) <= ORDER_FP64
+    if n > 1000:
+        assert ms[0] < 0.8 * ms[1], ms
+
+
 @pytest.mark.parametrize("n,M,tol,prec", [
     (150, 4200, 1e-8, 0), (150, 6200, 1e-8, 0), (90, 15000, 1e-8, 0), (60, 50000, 1e-8, 0),
     (150, 4200, 1e-4, 1), (90, 33000, 1e-4, 1),
