@@ -240,7 +240,7 @@ template <typename T, int D, int W>
 __global__ __launch_bounds__(kWaveThreads) void interp_wave_kernel(
     NuArgs a, const typename V2<T>::type* __restrict__ grid, int64_t set_stride,
     const int* __restrict__ cell, const T* __restrict__ pw, int rs, const double* __restrict__ x,
-    double* __restrict__ y, int grp) {
+    double* __restrict__ y, int grp, int64_t i0) {
   using V = typename V2<T>::type;
   constexpr int XL = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
   constexpr int ROWS = D == 1 ? 1 : (D == 2 ? W : W * W);
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kWaveThreads) void interp_wave_kernel(
   const int lane = threadIdx.x & 63;
   int64_t wid = xcd_item(blockIdx.x, grp) * (kWaveThreads / 64);
   wid += __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int64_t i = wid * PPW + lane / (XL * YL);
+  const int64_t i = i0 + wid * PPW + lane / (XL * YL);
   if (i >= a.n) return;  // whole groups
   grid += blockIdx.y * set_stride;
   x += blockIdx.y * a.n;
@@ -363,12 +363,19 @@ void launch_wave(const InterpCall& c) {
   constexpr int grp = 16;
   NuArgs a = nu_args(c.P, R);
   a.add_noise = c.add_noise;
-  hipLaunchKernelGGL((interp_wave_kernel<T, D, W>),
-                     dim3((unsigned)xcd_blocks((R.n + PPB - 1) / PPB, grp), (unsigned)c.nsets),
-                     dim3(kWaveThreads), 0, c.P->stream, a,
-                     static_cast<const typename V2<T>::type*>(c.grid), c.set_stride,
-                     R.cell.as<int>(), R.pw.as<T>(), R.rs, c.xs, c.ys, grp);
-  GP_CHECK_LAUNCH();
+  // a launch has fewer than 2^32 threads: with 16 lanes per point that is reached at 2.7e8
+  // points (slices of whole groups of blocks, so that none is done twice)
+  constexpr int64_t slice = ((int64_t)1 << 31) / kWaveThreads * PPB;
+  static_assert(slice % (8 * grp * PPB) == 0, "slices of whole groups of blocks");
+  for (int64_t i0 = 0; i0 < R.n; i0 += slice) {
+    const int64_t np = std::min(slice, R.n - i0);
+    hipLaunchKernelGGL((interp_wave_kernel<T, D, W>),
+                       dim3((unsigned)xcd_blocks((np + PPB - 1) / PPB, grp), (unsigned)c.nsets),
+                       dim3(kWaveThreads), 0, c.P->stream, a,
+                       static_cast<const typename V2<T>::type*>(c.grid), c.set_stride,
+                       R.cell.as<int>(), R.pw.as<T>(), R.rs, c.xs, c.ys, grp, i0);
+    GP_CHECK_LAUNCH();
+  }
 }
 
 // The blocks of interp_tile_kernel: 2x2 bins of 16^2 cells in 2-D, 2x2x1 bins

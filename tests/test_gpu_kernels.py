@@ -127,6 +127,29 @@ def test_interp_wide_windows_3d(gp, tol, n):
         assert ms[0] < 0.8 * ms[1], ms
 
 
+def test_interp_many_points(gp):
+    """270 million points (16 lanes each: more threads than one launch can have): outputs
+    at both ends and between them against the posterior mean at those points."""
+    import torch
+    n = 270_000_000
+    g = torch.Generator("cuda").manual_seed(0)
+    x = torch.rand(n, 1, dtype=torch.float64, device="cuda", generator=g)
+    one = torch.ones(n, dtype=torch.float64, device="cuda")
+    l = 0.05 * one
+    a = torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+    P = gp.Plan(x, one, l, 1.5, 0.1, 1e-8, M=100_000, n_sigma=0)
+    assert P.info()["w"] > 8
+    y = P.matvec(a)
+    i = torch.cat([torch.arange(500), torch.arange(0, n, n // 999), torch.arange(n - 500, n)]).cuda()
+    ref = P.posterior_mean(a, x[i].contiguous(), one[i].contiguous(), l[i].contiguous())
+    e = float((y[i] - ref).abs().max() / ref.abs().max())
+    say(f"{n} points: {e:.2e}")
+    assert e <= ORDER_FP64
+    P.close()
+    del P, x, one, l, a, y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("n,M,tol,prec", [
     (150, 4200, 1e-8, 0), (150, 6200, 1e-8, 0), (90, 15000, 1e-8, 0), (60, 50000, 1e-8, 0),
     (150, 4200, 1e-4, 1), (90, 33000, 1e-4, 1),
