@@ -22,6 +22,9 @@ template <> struct V2<float> { using type = float2; };
 constexpr int kSubThreads = 64;  // one wavefront per sub-tile
 constexpr int kGCmax = 8;        // grid pairs per wavefront
 constexpr int kSpreadBatch = 16;  // points per batch of the spreading
+// A launch has fewer than 2^32 threads: one wavefront per sub-tile reaches that at
+// 6.7e7 sub-tiles (3-D grids of 1625^3 cells on); launches take 2^31 threads each.
+constexpr int64_t kSliceBlocks = ((int64_t)1 << 31) / kSubThreads;
 
 // Sub-tile blk = bin * nsub + sub (sub-tiles of a bin consecutive, first
 // dimension fastest): its first cell s0 and its bin's coordinates tcoord.  32-bit
@@ -69,10 +72,10 @@ __device__ __forceinline__ unsigned xcd_grouped(unsigned bid, unsigned grp) {
 // window cell relative to s0 - (w - 1), 8 bits per dimension}.
 template <int D, bool FILL>
 __global__ __launch_bounds__(kSubThreads) void spread_list_build_kernel(
-    NuArgs a, int st, const int* __restrict__ cell, const int* __restrict__ bin_start,
+    NuArgs a, int st, int64_t blk0, const int* __restrict__ cell, const int* __restrict__ bin_start,
     int* __restrict__ cnt, const int64_t* __restrict__ off, int2* __restrict__ list) {
   extern __shared__ int ismem[];
-  const int64_t blk = blockIdx.x;
+  const int64_t blk = blk0 + blockIdx.x;
   int s0[3], tcoord[3];
   sub_tile_origin(a, D, st, blk, s0, tcoord);
   const int w = a.w;
@@ -200,7 +203,7 @@ template <int NM> struct AccOf<float, NM> { using type = Acc32<NM>; };
 // arithmetic 125 cycles, LDS 145, loads 100, matrix 64, in 330.
 template <typename T, int D, int NM, int KW, bool FULL, typename Off>
 __global__ __launch_bounds__(kSubThreads, NM > 2 || (sizeof(T) == 8 && KW > 2) ? 3 : (sizeof(T) == 4 && KW == 1 ? 5 : 4)) void spread_list_kernel(
-    NuArgs a, int lg_, int grp, unsigned nitems, int per, int64_t set_stride, const double* __restrict__ x,
+    NuArgs a, int lg_, int grp, unsigned bid0, unsigned nitems, int per, int64_t set_stride, const double* __restrict__ x,
     const T* __restrict__ pw, int rs, const int64_t* __restrict__ off, const int2* __restrict__ list,
     const int4* __restrict__ items, typename V2<T>::type* __restrict__ part,
     typename V2<T>::type* __restrict__ grid) {
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(kSubThreads, NM > 2 || (sizeof(T) == 8 && KW > 2) ?
   // their number (both write the same values)
   const int g0 = min((int)blockIdx.y * a.gc, a.npair - a.gc);
   const int lane = threadIdx.x, n = lane & 15, q = lane >> 4;
-  unsigned blk = xcd_grouped(blockIdx.x, (unsigned)grp), nsub = 1;
+  unsigned blk = xcd_grouped(bid0 + blockIdx.x, (unsigned)grp), nsub = 1;
   int slot = -1;
   int64_t lo, hi;
   int64_t ends = 0;  // lane k: end of the list of sub-tile blk + k
@@ -573,11 +576,13 @@ void launch_sub(Plan* P, const Records& R, const double* xs, int nsets) {
     for (int set = 0; set < nsets; set += group) {
       const unsigned ns = (unsigned)std::min(group, nsets - set);
       V* gset = grid + set * set_stride;
-      hipLaunchKernelGGL(kern, dim3((unsigned)nblk, nch, ns), dim3(kSubThreads), smem, P->stream, a, lg,
-                         grp, (unsigned)ni, per, set_stride, xs + set * R.n, R.pw.as<T>(), R.rs,
-                         R.sub_off.as<int64_t>(), R.sub_list.as<int2>(),
-                         split ? R.sp_work.as<int4>() : nullptr, part, gset);
-      GP_CHECK_LAUNCH();
+      for (int64_t b = 0; b < nblk; b += kSliceBlocks) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(kSliceBlocks, nblk - b), nch, ns), dim3(kSubThreads),
+                           smem, P->stream, a, lg, grp, (unsigned)b, (unsigned)ni, per, set_stride,
+                           xs + set * R.n, R.pw.as<T>(), R.rs, R.sub_off.as<int64_t>(), R.sub_list.as<int2>(),
+                           split ? R.sp_work.as<int4>() : nullptr, part, gset);
+        GP_CHECK_LAUNCH();
+      }
       if (R.n_sp_red > 0) {
         hipLaunchKernelGGL((spread_reduce_kernel<T, D>), dim3((unsigned)R.n_sp_red, 1, ns), dim3(256), 0,
                            P->stream, a, lg, set_stride, R.sp_red.as<int4>(), part, gset);
@@ -615,9 +620,12 @@ void launch_sub(Plan* P, const Records& R, const double* xs, int nsets) {
 template <int D, bool FILL>
 void launch_list_build(const NuArgs& a, int st, int64_t nsub, size_t smem, hipStream_t s, const Records& R,
                        int* cnt, const int64_t* off, int2* list) {
-  hipLaunchKernelGGL((spread_list_build_kernel<D, FILL>), dim3((unsigned)nsub), dim3(kSubThreads), smem, s,
-                     a, st, R.cell.as<int>(), R.bin_start.as<int>(), cnt, off, list);
-  GP_CHECK_LAUNCH();
+  for (int64_t b = 0; b < nsub; b += kSliceBlocks) {
+    hipLaunchKernelGGL((spread_list_build_kernel<D, FILL>), dim3((unsigned)std::min(kSliceBlocks, nsub - b)),
+                       dim3(kSubThreads), smem, s, a, st, b, R.cell.as<int>(), R.bin_start.as<int>(), cnt, off,
+                       list);
+    GP_CHECK_LAUNCH();
+  }
 }
 template <bool FILL>
 void list_build(int d, const NuArgs& a, int st, int64_t nsub, size_t smem, hipStream_t s, const Records& R,

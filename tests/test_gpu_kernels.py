@@ -290,6 +290,23 @@ def test_spread_lists_match_atomics(gp, d, n, M, n_sigma, tol, prec):
         assert e <= bar and el <= bar, (e, el)
 
 
+def test_spread_many_sub_tiles(gp):
+    """A 3-D grid of 1648^3 cells: more than 2^32 / 64 sub-tiles, so that a launch of a
+    wavefront each has more threads than one launch can have."""
+    n = 3000
+    prob = inputs.random_small(3, n, seed=11, nu=1.5, lmin=0.1, lmax=0.25, constant_scales=True)
+    prob.x[: n // 2] = 0.5 + 0.5 * prob.x[: n // 2]  # more of them where the sub-tiles' numbers are high
+    prob.x[0], prob.x[-1] = 0.0, 1.0
+    a = np.random.default_rng(2).standard_normal(n)
+    kw = dict(tol=1e-4, precision=1, M=385, dw=0.4)
+    got, info = _matvec(gp, prob, a, **kw)
+    assert info["na"][0] * info["na"][1] * info["na"][2] / 64 * 64 >= 2 ** 32
+    ref, _ = _matvec(gp, prob, a, spread=1, **kw)
+    e = max_rel(got, ref)
+    say(f"na={info['na']} {info['device_bytes'] / 2**30:.0f} GiB: {e:.2e}")
+    assert e <= ORDER_FP32
+
+
 def _fits_lean(gp, prob, info, kw):
     """Whether the plan without lists is the smaller one (dense points)."""
     kw = dict(kw)
