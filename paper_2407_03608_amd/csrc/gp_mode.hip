@@ -325,6 +325,14 @@ __global__ __launch_bounds__(kThreads) void mode_radial2_kernel(
   }
 }
 
+// LDS accesses of the wave's lanes before it are done before those after it.  A wave's
+// LDS operations complete in order, so this only binds the compiler (no instruction).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // fp64, d = 2 and 3: a wave takes 64 / 2^(d-1) orthant points, a point's sign
 // patterns on adjacent lanes.  The rows of A it needs come through LDS, 128 bytes
 // of every row at a time: eight lanes load one row's 128 bytes (16 each), the next
@@ -436,10 +444,10 @@ __global__ __launch_bounds__(kThreads) void mode_rows_kernel(
           // whole row in registers
 #pragma unroll
           for (int k = 0; k < NK; ++k) asm volatile("" : "+v"(acc[k].x), "+v"(acc[k].y));
-          __builtin_amdgcn_wave_barrier();
+          wave_lds_sync();
 #pragma unroll
           for (int i = 0; i < NLD; ++i) own[lane + 64 * i] = next[i];
-          __builtin_amdgcn_wave_barrier();
+          wave_lds_sync();
           if (ch + 1 < NCH) {
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
