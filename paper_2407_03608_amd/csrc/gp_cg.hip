@@ -61,8 +61,9 @@ __device__ __forceinline__ double part_sum(int nparts, const double* __restrict_
   return block_sum<kRedThreads>(v);
 }
 
-// S layout: 0 rr, 3 bb, 5 scratch, 6 stopping threshold on rr, 7 done flag,
-// 8 completed iterations, 10 + k: rr at the start of iterations of parity k
+// S layout: 0 rr, 3 bb, 5 scratch, 6 stopping threshold on rr, 7 done flag (for the
+// host), 8 completed iterations; at the start of iterations of parity k: 10 + k rr,
+// 12 + k done flag
 // S[slot] = sum of the partial sums
 __global__ __launch_bounds__(kRedThreads) void dot_final(int nparts, const double* __restrict__ part,
                                                          double* __restrict__ S, int slot) {
@@ -81,16 +82,23 @@ __global__ void cg_init_flags(int m, double* S, double tol) {
   s[7] = (s[3] == 0.0 || s[0] <= s[6]) ? 1.0 : 0.0;
   s[8] = 0.0;
   s[10] = s[0];
+  s[12] = s[13] = s[7];
 }
 
 // The end of an iteration: rr = its new value, one more iteration, done if it
-// meets the threshold.  The next iteration's parity slot gets rr, so that no
-// workgroup that still reads the old one is in its way.
+// meets the threshold.  The next iteration's parity slots get rr and the flag, so
+// that no workgroup that still reads the old ones is in its way.
 __device__ __forceinline__ void cg_iteration_done(double* __restrict__ S, double rr, int parity) {
+  const bool done = rr <= S[6];
   S[0] = rr;
   S[10 + (parity ^ 1)] = rr;
+  S[12 + (parity ^ 1)] = done ? 1.0 : 0.0;
   S[8] += 1.0;
-  if (rr <= S[6]) S[7] = 1.0;
+  if (done) S[7] = 1.0;
+}
+// An iteration after the last: the flag goes on to the next one's slot.
+__device__ __forceinline__ void cg_iteration_skipped(double* __restrict__ S, int parity) {
+  S[12 + (parity ^ 1)] = 1.0;
 }
 
 // x += a p ; r -= a Ap ; partial sums of r.r, with a = rr / p.Ap; every workgroup
@@ -106,7 +114,7 @@ __global__ __launch_bounds__(kRedThreads) void update_xr(int64_t n, int nparts, 
                                                          double* __restrict__ part) {
   const int64_t col = blockIdx.y;
   S += col * kCgScalars;
-  if (S[7] != 0.0) return;
+  if (S[12 + parity] != 0.0) return;
   x += col * n;
   r += col * n;
   p += col * n;
@@ -131,8 +139,10 @@ __global__ __launch_bounds__(kRedThreads) void update_p(int64_t n, int nparts, i
                                                         double* __restrict__ p) {
   const int64_t col = blockIdx.y;
   S += col * kCgScalars;
-  // the flag may be raised by this launch's first workgroup: p is then not used again
-  if (S[7] != 0.0) return;
+  if (S[12 + parity] != 0.0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) cg_iteration_skipped(S, parity);
+    return;
+  }
   r += col * n;
   p += col * n;
   const double rr = part_sum(nparts, part + col * kCgPart);
@@ -157,7 +167,7 @@ __global__ __launch_bounds__(kSmallThreads) void cg_step_small(int64_t n, int pa
                                                                const double* __restrict__ Ap) {
   const int64_t col = blockIdx.y;
   S += col * kCgScalars;
-  const double done = S[7], rr0 = S[10 + parity];
+  const double done = S[12 + parity], rr0 = S[10 + parity];
   x += col * n;
   r += col * n;
   p += col * n;
@@ -172,7 +182,10 @@ __global__ __launch_bounds__(kSmallThreads) void cg_step_small(int64_t n, int pa
     xv[k] = in ? x[i] : 0.0;
     rv[k] = in ? r[i] : 0.0;
   }
-  if (done != 0.0) return;
+  if (done != 0.0) {
+    if (threadIdx.x == 0) cg_iteration_skipped(S, parity);
+    return;
+  }
   double v = 0;
 #pragma unroll
   for (int k = 0; k < kSmallPer; ++k) v += pv[k] * av[k];
@@ -194,7 +207,7 @@ __global__ __launch_bounds__(kSmallThreads) void cg_step_small(int64_t n, int pa
       p[i] = rv[k] + b * pv[k];
     }
   }
-  if (threadIdx.x == 0) cg_iteration_done(S, rr, parity);  // the flag was read before the sums' barriers
+  if (threadIdx.x == 0) cg_iteration_done(S, rr, parity);
 }
 
 // r = b - Ax

@@ -260,6 +260,40 @@ def test_cg_vector_kernels(gp, n):
         assert max_rel(got[j], x) < 1e-11, (n, j, max_rel(got[j], x))
 
 
+@pytest.mark.parametrize("n,replace", [(300, 0), (300, 3), (4096, 0), (4097, 0), (4097, 3), (6000, 2)])
+def test_cg_stops_once(gp, n, replace):
+    """Iterations queued beyond the last one change nothing, whichever parity the last
+    has: K iterations with max_iter = K have the bits of the converged solve, and a
+    column of a lockstep solve that is done (at once: b = 0, or at another iteration than
+    its neighbours) keeps its iterate and its count while the others go on."""
+    prob = inputs.random_small(1, n, seed=n, nu=2.5, lmin=0.1, lmax=0.25, eta=0.3)
+    P = gp.Plan(cuda(prob.x), cuda(prob.sigma), cuda(prob.l), prob.nu, prob.eta, 1e-8, M=60)
+    rng = np.random.default_rng(n)
+    smooth = np.sin(3 * prob.x[:, 0])
+    B = np.stack([rng.standard_normal(n), np.zeros(n), smooth, smooth + 0.01 * rng.standard_normal(n)])
+    counts = set()
+    single = []
+    for tol in (1e-3, 1e-5, 1e-6, 1e-8):
+        for b in B[[0, 2, 3]]:
+            full, info = P.cg_solve(cuda(b), tol=tol, max_iter=500, replace_every=replace)
+            k = info["iters"]
+            counts.add(k % 2)
+            if k == 0:
+                continue
+            try:
+                part, pinfo = P.cg_solve(cuda(b), tol=tol, max_iter=k, replace_every=replace)
+            except gp.GpError as e:
+                raise AssertionError((n, tol, k)) from e
+            assert pinfo["iters"] == k and np.array_equal(host(full), host(part))
+    assert counts == {0, 1}
+    if replace == 0:
+        X, iters, _, _ = P.cg_solve_multi(cuda(B), tol=1e-6, max_iter=500)
+        single = [P.cg_solve(cuda(b), tol=1e-6, max_iter=500) for b in B]
+        assert len({int(i) for i in iters}) > 2
+        for j in range(4):
+            assert int(iters[j]) == single[j][1]["iters"] and np.array_equal(host(X)[j], host(single[j][0])), j
+
+
 @pytest.mark.parametrize("d,n,M,n_sigma,tol,prec", [
     # 1 .. 12 grid pairs (one chunk of up to 8, two chunks, a chunk that overlaps the other)
     (1, 700, 60, 1, 1e-8, 0), (1, 700, 5000, 23, 1e-8, 0), (1, 2500, 40, 17, 1e-4, 1), (1, 300, 6, 3, 1e-3, 1),
