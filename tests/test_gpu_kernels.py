@@ -176,9 +176,12 @@ def test_four_step_against_oracle(gp, n, M, tol, prec):
     # every remainder of the columns by blocks of 8, lengths 24 .. 1536
     (2, 4, 1e-4, 0), (2, 11, 1e-6, 0), (2, 18, 1e-6, 0), (2, 33, 1e-4, 0), (2, 62, 1e-8, 0), (2, 126, 1e-6, 0),
     (2, 5, 1e-3, 1), (2, 24, 1e-4, 1), (2, 60, 1e-4, 1), (2, 129, 1e-4, 1), (2, 302, 1e-4, 1), (2, 301, 1e-8, 0),
-    # 2048 .. 8192: several columns per thread, per workgroup and one
+    # 2048 .. 8192: several columns per thread, per workgroup and one (M odd: against blocks
+    # of 4 columns, M even: against whole rows)
     (2, 801, 1e-8, 0), (2, 1100, 1e-6, 0), (2, 1701, 1e-6, 0), (2, 2501, 1e-6, 0), (2, 3001, 1e-4, 0),
+    (2, 800, 1e-8, 0), (2, 1600, 1e-6, 0), (2, 1702, 1e-6, 0), (2, 2046, 1e-8, 0), (2, 3000, 1e-4, 0),
     (2, 802, 1e-4, 1), (2, 1104, 1e-4, 1), (2, 1905, 1e-4, 1), (2, 2400, 1e-4, 1), (2, 3002, 1e-4, 1),
+    (2, 1602, 1e-4, 1), (2, 2046, 1e-4, 1),
     # rows of modes unpadded and padded to whole lines
     (3, 4, 1e-4, 0), (3, 13, 1e-6, 0), (3, 66, 1e-6, 0), (3, 90, 1e-4, 0),
     (3, 5, 1e-3, 1), (3, 71, 1e-4, 1), (3, 116, 1e-4, 1),
@@ -186,20 +189,26 @@ def test_four_step_against_oracle(gp, n, M, tol, prec):
 def test_fft_layouts(gp, d, M, tol, prec):
     """Transforms through blocks of columns (2-D) and padded rows of modes (3-D)
     against the oracle or, at sizes beyond it, against the plan whose byte limit
-    leaves the rows of B whole and unpadded."""
+    leaves no room for them, with the same spreading (the LDS-atomic variant): rows of B
+    whole, in 2-D where M is even, or in blocks of 4 columns, and rows of modes unpadded."""
     n = 200 if (2 * M + 1) ** d < 20000 else 20000
     prob = inputs.random_small(d, n, seed=M, nu=1.5, lmin=0.1, lmax=0.25)
     kw = dict(tol=tol, precision=prec, M=M, dw=0.25)
     a = np.random.default_rng(3).standard_normal(n)
-    got, info = _matvec(gp, prob, a, **kw)
     if n == 200:
+        got, info = _matvec(gp, prob, a, **kw)
         ref, bar = O.ktilde_matvec(oracle_params(info), prob.x, prob.sigma, prob.l, a), 100 * tol
         ref = ref + prob.eta ** 2 * a
     else:
-        kw["spread"] = 1  # the same spreading in both
-        ref, info = _matvec(gp, prob, a, **kw)
+        kw["spread"] = 1
+        got, info = _matvec(gp, prob, a, **kw)
         ref, linfo = _matvec(gp, prob, a, max_device_bytes=info["device_bytes"] - 1, **kw)
         assert linfo["device_bytes"] < info["device_bytes"]
+        if d == 2:  # what the limit leaves: rows whole (mc + 1 columns counted) or blocks of 4
+            mc, na1 = 2 * M + 1, info["na"][1]
+            blocks = info["n_pairs"] * na1 * ((mc + 7) // 8 * 8 - (mc + 1)) * (8 if prec else 16)
+            assert info["device_bytes"] - linfo["device_bytes"] == blocks
+            assert (mc + 3) // 4 * 4 > mc + 1 or M % 2 == 1
         bar = ORDER_FP32 if prec else ORDER_FP64
     e = max_rel(got, ref)
     say(f"layouts d={d} M={M} nf={info['nf'][0]} na={info['na']} prec={prec}: {e:.2e}")
