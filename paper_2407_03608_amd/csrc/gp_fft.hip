@@ -211,8 +211,8 @@ __device__ __forceinline__ void buf_store(double2 v, __amdgpu_buffer_rsrc_t r, u
 
 struct KParams {
   int64_t ntrans, inner, in_os, out_os, in_es, in_cs, out_es, out_cs;
-  int64_t in_cs1, in_es1, out_cs1, out_es1;
-  int in_cps, in_ips, out_cps, out_ips;  // log2 of the interleave factors
+  int64_t in_cs1, out_es1;
+  int in_cps, out_ips;  // log2 of the interleave factors
   int n_in, in_start, n_out, out_start, sign;
   // four-step passes (1-D): rows per grid, transform length, kept modes -M..M
   int tw4_mod, nf4, band;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
   const bool act = t < p.ntrans;
   const int64_t o = act ? t / p.inner : 0, c = act ? t - o * p.inner : 0;
   const V* src = in + o * p.in_os + (c >> p.in_cps) * p.in_cs + (c & ((1 << p.in_cps) - 1)) * p.in_cs1;
-  V* dst = out + o * p.out_os + (c >> p.out_cps) * p.out_cs + (c & ((1 << p.out_cps) - 1)) * p.out_cs1;
+  V* dst = out + o * p.out_os + c * p.out_cs;
   const int row4 = MODE == kFour ? (int)(o % p.tw4_mod) : 0;
   constexpr int R1 = next_radix(L, EPT);
   constexpr int NB1 = EPT / R1;
@@ -445,13 +445,12 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
     const int64_t t0 = bid * B;
     const int64_t o0 = t0 / p.inner, c0 = t0 - o0 * p.inner;
     const V* ib = in + o0 * p.in_os + (c0 >> p.in_cps) * p.in_cs + (c0 & ((1 << p.in_cps) - 1)) * p.in_cs1;
-    V* ob = out + o0 * p.out_os + (c0 >> p.out_cps) * p.out_cs + (c0 & ((1 << p.out_cps) - 1)) * p.out_cs1;
+    V* ob = out + o0 * p.out_os + c0 * p.out_cs;
     const __amdgpu_buffer_rsrc_t irsrc = buf_rsrc(ib);
     orsrc = buf_rsrc(ob);
     const int idl = (int)(src - ib);
     odl = (int)(dst - ob);
-    const int pm = (1 << p.in_ips) - 1;
-    const int ies = (int)p.in_es, ies1 = (int)p.in_es1;
+    const int ies = (int)p.in_es;
     const int i0 = jt - p.in_start;
 #pragma unroll
     for (int u = 0; u < NB1; ++u)
@@ -459,7 +458,7 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
       for (int m = 0; m < R1; ++m) {
         int i = i0 + TPT * u + m * (L / R1);
         i = i < 0 ? i + L : i;
-        const int off = idl + (i >> p.in_ips) * ies + (i & pm) * ies1;
+        const int off = idl + i * ies;
         v[u * R1 + m] = buf_load(irsrc, act && i < p.n_in ? (unsigned)off * (unsigned)sizeof(V) : kBufOut,
                                  (V*)nullptr);
       }
@@ -473,7 +472,7 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
       int i = pos - p.in_start;
       if (i < 0) i += L;
       V val = V{T(0), T(0)};
-      if (act && i < p.n_in) val = src[elem_off(i, p.in_ips, p.in_es, p.in_es1)];
+      if (act && i < p.n_in) val = src[i * p.in_es];
       v[u * R1 + m] = val;
     }
   }
@@ -639,8 +638,8 @@ bool buf_fits(const KParams& p, const FftPass& q, int B, int64_t vb) {
     const int64_t emax = n > 0 ? ((int64_t)(n - 1) >> ips) * es + (((int64_t)1 << ips) - 1) * es1 : 0;
     return (span + emax + 1) * vb < (int64_t)kBufRange - 64;
   };
-  return side(p.in_os, p.in_cs, p.in_cs1, p.in_cps, p.in_es, p.in_es1, p.in_ips, p.n_in) &&
-         side(p.out_os, p.out_cs, p.out_cs1, p.out_cps, p.out_es, p.out_es1, p.out_ips, p.n_out);
+  return side(p.in_os, p.in_cs, p.in_cs1, p.in_cps, p.in_es, 0, 0, p.n_in) &&
+         side(p.out_os, p.out_cs, 0, 0, p.out_es, p.out_es1, p.out_ips, p.n_out);
 }
 
 template <typename T, int L, int EPT, int B>
@@ -685,8 +684,8 @@ template <typename T, int L, int EPT, int NC, int WV>
 bool launch_cols(const FftPass& q, const KParams& p, const void* in, void* out, const void* tw,
                  hipStream_t s) {
   using V = typename V2<T>::type;
-  if (q.tw4 != nullptr || q.inner < 2 || (1 << p.in_cps) % NC != 0 || p.in_cs1 != 1 || p.in_ips != 0 ||
-      p.out_cps != 0 || p.out_ips != 0 || !buf_fits(p, q, NC, (int64_t)sizeof(V)))
+  if (q.tw4 != nullptr || q.inner < 2 || (1 << p.in_cps) % NC != 0 || p.in_cs1 != 1 || p.out_ips != 0 ||
+      !buf_fits(p, q, NC, (int64_t)sizeof(V)))
     return false;
   const dim3 g((unsigned)(q.n_outer * ((q.inner + NC - 1) / NC))), t(L / EPT);
   const V *i = static_cast<const V*>(in), *w = static_cast<const V*>(tw);
@@ -713,13 +712,9 @@ void launch_len(const FftPass& q, const void* in, void* out, const void* tw, hip
   p.out_es = q.out_es ? q.out_es : q.inner;
   p.out_cs = q.out_cs ? q.out_cs : 1;
   p.in_cs1 = q.in_cs1;
-  p.in_es1 = q.in_es1;
-  p.out_cs1 = q.out_cs1;
   p.out_es1 = q.out_es1;
   auto log2i = [](int v) { return v <= 1 ? 0 : 31 - __builtin_clz((unsigned)v); };
   p.in_cps = log2i(q.in_cp);
-  p.in_ips = log2i(q.in_ip);
-  p.out_cps = log2i(q.out_cp);
   p.out_ips = log2i(q.out_ip);
   p.n_in = q.n_in;
   p.in_start = ((q.in_start % L) + L) % L;
@@ -830,7 +825,7 @@ void fft_pass(int fp64, const FftPass& p, const void* in, void* out, const void*
               hipStream_t s) {
   if (p.n_in > p.L || p.n_out > p.L || p.n_in < 0 || p.n_out < 0)
     throw Error{GP_EINVAL, "fft_pass: window longer than the transform"};
-  for (int f : {p.in_cp, p.in_ip, p.out_cp, p.out_ip})
+  for (int f : {p.in_cp, p.out_ip})
     if (f < 1 || (f & (f - 1)) != 0) throw Error{GP_EINVAL, "fft_pass: interleave factors are powers of two"};
   if (fp64)
     dispatch<double>(p, in, out, twiddles, s);

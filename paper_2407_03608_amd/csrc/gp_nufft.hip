@@ -718,8 +718,10 @@ void spread_dispatch(Plan* P, const Records& R, const double* xs, int nsets = 1)
     if (owner) {
       const double* x = xs + j * R.n;
       if (P->d == 1) launch_spread_owner<T, 1, 1>(P, R, x);
-      else if (P->d == 2) launch_spread_owner<T, 2, 1>(P, R, x);
-      else two ? launch_spread_owner<T, 3, 2>(P, R, x) : launch_spread_owner<T, 3, 1>(P, R, x);
+      if constexpr (sizeof(T) == 8) {  // fp32 plans in d >= 2 always have lists
+        if (P->d == 2) launch_spread_owner<T, 2, 1>(P, R, x);
+        else if (P->d == 3) two ? launch_spread_owner<T, 3, 2>(P, R, x) : launch_spread_owner<T, 3, 1>(P, R, x);
+      }
       continue;
     }
     if (P->d == 1) launch_spread<T, 1>(P, R, xs + j * R.n);
