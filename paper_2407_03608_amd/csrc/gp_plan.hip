@@ -76,14 +76,18 @@ void DevBuf::release() {
   s = nullptr;
 }
 
-void retag_plan_stream(Plan* P, hipStream_t st) {
+// Every device buffer that a plan holds.
+static std::vector<DevBuf*> plan_buffers(Plan* P) {
   Records& R = P->rec;
-  DevBuf* bufs[] = {&R.perm, &R.cell, &R.pw, &R.bin_start, &R.sp_work, &R.sp_red, &R.in_work,
+  return {&R.perm, &R.cell, &R.pw, &R.bin_start, &R.sp_work, &R.sp_red, &R.in_work,
                     &R.in_work2, &R.part, &R.sub_off, &R.sub_list, &P->nodes_d, &P->bary_d,
                     &P->gtab, &P->etab, &P->vtd, &P->lr_off, &P->atab, &P->rowidx, &P->mode_tiles, &P->dec,
                     &P->tw[0], &P->tw[1], &P->tw[2], &P->tw4, &P->gridA, &P->gridB, &P->gridB2,
                     &P->gridC, &P->mA, &P->mB, &P->mB2, &P->mC, &P->mpart, &P->vec, &P->cg_part, &P->cg_S};
-  for (DevBuf* b : bufs)
+}
+
+void retag_plan_stream(Plan* P, hipStream_t st) {
+  for (DevBuf* b : plan_buffers(P))
     if (b->p) b->s = st;
 }
 
@@ -567,9 +571,10 @@ void build_records_into(Plan* P, int64_t n, const double* pts, const double* sig
 
 // ------------------------------------------------------------ build_plan ----
 
-int build_plan(int d, int64_t n, const double* pts, const double* sigma, const double* l,
-               double nu, double eta, double tol, const gp_opts* opts_in, Plan* P,
-               bool query_only, size_t* bytes_out) {
+// lean: without spreading lists, column blocks and padded rows, whatever the limit
+static int build_plan_as(bool lean, int d, int64_t n, const double* pts, const double* sigma,
+                         const double* l, double nu, double eta, double tol, const gp_opts* opts_in,
+                         Plan* P, bool query_only, size_t* bytes_out) {
   gp_opts opts;
   if (opts_in)
     opts = *opts_in;
@@ -682,7 +687,7 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
                        (d >= 2 && P->precision == GP_FP32_BULK ? spread_list_bound_bytes(P, n, false) : 0);
   P->lean_bytes = base + grid_bytes(true) + plain;
   bytes = base + grid_bytes(false) + (atomic ? plain : spread_list_bound_bytes(P, n, true));
-  if (opts.max_device_bytes > 0 && bytes > opts.max_device_bytes) {
+  if (lean || (opts.max_device_bytes > 0 && bytes > opts.max_device_bytes)) {
     P->lean = true;
     grid_bytes(true);
     bytes = P->lean_bytes;
@@ -836,6 +841,20 @@ int build_plan(int d, int64_t n, const double* pts, const double* sigma, const d
   P->cg_hS = pinned_scalars_get();
   GP_HIP(hipStreamSynchronize(s));
   return GP_OK;
+}
+
+// Where the device itself has no room for the lists and the larger layouts, the plan
+// without them is built, as under a limit.
+int build_plan(int d, int64_t n, const double* pts, const double* sigma, const double* l,
+               double nu, double eta, double tol, const gp_opts* opts, Plan* P, bool query_only,
+               size_t* bytes_out) {
+  try {
+    return build_plan_as(false, d, n, pts, sigma, l, nu, eta, tol, opts, P, query_only, bytes_out);
+  } catch (const Error& e) {
+    if (e.code != GP_ENOMEM || query_only || P->lean || P->lean_bytes >= P->device_bytes) throw;
+  }
+  for (DevBuf* b : plan_buffers(P)) b->release();
+  return build_plan_as(true, d, n, pts, sigma, l, nu, eta, tol, opts, P, query_only, bytes_out);
 }
 
 }  // namespace gp

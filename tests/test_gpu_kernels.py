@@ -437,6 +437,55 @@ def test_byte_limit_admits_plans_without_lists(gp, d, n, M, tol, prec, dw, n_sig
         gp.Plan(*arg, max_device_bytes=least - 1, **kw)
 
 
+def _trim_pool():
+    """Hands the memory that the runtime's pool keeps for reuse back to the device."""
+    import ctypes
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    pool = ctypes.c_void_p()
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), 0) == 0
+    assert hip.hipMemPoolTrimTo(pool, ctypes.c_size_t(0)) == 0
+
+
+def test_plan_where_lists_do_not_fit_the_device(gp):
+    """A plan without a byte limit on a device whose free memory holds its form without
+    spreading lists, but not the one with them: built, as it was before there were
+    lists, with the values of the plan with lists."""
+    import torch
+    n = 6_000_000
+    g = torch.Generator("cuda").manual_seed(1)
+    x = torch.rand(n, 3, dtype=torch.float64, device="cuda", generator=g)
+    one = torch.ones(n, dtype=torch.float64, device="cuda")
+    l = 0.2 * one
+    a = torch.randn(n, dtype=torch.float64, device="cuda", generator=g)
+    arg = (x, one, l, 2.5, 0.1, 1e-8)
+    kw = dict(M=60, dw=0.25, n_sigma=0)
+    P = gp.Plan(*arg, **kw)
+    full = P.info()["device_bytes"]
+    want = P.matvec(a)
+    P.close()
+    lean = gp.plan_query(*arg, max_device_bytes=1, **kw)
+    # the sort's work arrays and the CG's come on top of what a plan counts; the query's
+    # bound of the lists is above what they take
+    room = lean + (full - lean) // 4
+    say(f"with lists at most {full >> 20} MB, without {lean >> 20} MB, room {room >> 20} MB")
+    torch.cuda.synchronize()
+    _trim_pool()
+    free = torch.cuda.mem_get_info()[0]
+    filler = torch.empty(free - room, dtype=torch.uint8, device="cuda")
+    try:
+        P = gp.Plan(*arg, **kw)
+        info = P.info()
+        say(f"built with {info['device_bytes'] >> 20} MB counted, {torch.cuda.mem_get_info()[0] >> 20} MB left")
+        assert info["device_bytes"] == lean
+        got = P.matvec(a)
+        assert float((got - want).abs().max() / want.abs().max()) <= ORDER_FP64
+        P.close()
+    finally:
+        del filler
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("d,n,m,prec", [(1, 300, 1, 0), (2, 3000, 5000, 0), (2, 900, 40, 1), (3, 500, 300, 0)])
 def test_posterior_mean_streams(gp, d, n, m, prec):
     """The targets are read on a stream beside the plan's: they may be written by
