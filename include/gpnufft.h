@@ -93,12 +93,16 @@ typedef struct {
   int use_box;              /* 1: map the box [box_lo, box_hi] (not the data's) onto [-1,1]^d */
   double box_lo[3], box_hi[3];
   double l_lo, l_hi;        /* widen the length-scale range (posterior targets); 0 = unused */
-  size_t max_device_bytes;  /* admission limit for the plan's device memory; 0 = none */
+  size_t max_device_bytes;  /* admission limit for the plan's device memory; 0 = none.  A plan
+                               over it is tried without spreading lists per sub-tile (fp32 grids
+                               in d >= 2: with lists that are not split), blocks of columns and
+                               padded rows (as is one whose lists do not fit the device):
+                               same operator, other rounding, slower */
   int spread;               /* type-1 spreading variant (GP_SPREAD_*): 0 = automatic
                                (GP_SPREAD_OWNER); 1 = per-(point, row) work items with LDS
-                               atomics; 2 = each thread owns grid cells of a tile (or, for
-                               fp32 grids in d >= 2, of a sub-tile with one wavefront each)
-                               and sums in registers in a fixed order (deterministic) */
+                               atomics; 2 = one wavefront owns the cells of a sub-tile and sums
+                               the points of its list in a fixed order (deterministic; plans
+                               without lists: a workgroup owns a tile, in a fixed order too) */
   int interp;               /* type-2 interpolation: 0 = default (where many points share
                                their cells, blocks of bins plus halo staged in LDS one grid
                                pair at a time; else a group of lanes per point reading its

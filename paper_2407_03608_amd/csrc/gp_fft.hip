@@ -229,7 +229,7 @@ enum { kPlain = 0, kBuf = 1, kFour = 2, kCols = 3 };
 // radix R1, so that lanes that hold B columns of consecutive j store at strides
 // (R1 + 1) B and load at strides B, both free of bank conflicts (one padded
 // buffer per sequence: d=3 M=189 fp64, L=768, 8 columns per workgroup 2.03 / 2.67 /
-// 2.67 / 1.97 -> 1.62 / 2.26 / 2.09 / 1.49 ms for the four strided passes; d=2
+// 2.67 / 1.97 -> 1.60 / 2.22 / 2.07 / 1.46 ms for the four strided passes; d=2
 // L=2048 fp64, 112 grids 2.22 / 1.67 -> 1.72 / 1.29).
 template <int PU>
 __device__ __forceinline__ constexpr int lay(int pos) { return pos + pos / PU; }
@@ -487,7 +487,8 @@ __global__ __launch_bounds__(B*(L / EPT), fft_waves(L, EPT, B, (int)sizeof(T))) 
 // LDS buffer of a single column.  The strided passes are bound by cache-line
 // requests, and this halves them.  d=2 N=1e6 fp64 (7 grids, M=2047, L=6144):
 // 1.04 -> 0.95 ms forward, 0.84 -> 0.87 inverse; fp32 0.35 -> 0.30 and 0.28 -> 0.26;
-// four fp32 columns 0.31 / 0.27; 3072-point fp64 columns lose (0.34 -> 0.36 and 0.22 ->
+// (one column per workgroup for the fp64 inverse: 0.84, but the other passes take as much
+// longer, 5.37 ms per iteration either way); four fp32 columns 0.31 / 0.27; 3072-point fp64 columns lose (0.34 -> 0.36 and 0.22 ->
 // 0.27: two waves per SIMD instead of four).
 template <typename T, typename V, int L, int EPT, int NC, int Ls, int S>
 __device__ __forceinline__ void col_stages(V (&v)[NC][EPT], T* __restrict__ buf, int jt,

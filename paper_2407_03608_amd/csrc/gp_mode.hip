@@ -338,10 +338,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 // of every row at a time: eight lanes load one row's 128 bytes (16 each), the next
 // chunk is in flight while the current one is used, and each lane then reads its
 // own row (slots permuted by the row so that the lanes fall on different banks).
-// The kernels above, whose lanes each gather their own row, are bound by the cache
-// lines looked up per load; this one by memory, 4.0 TB/s over the grid and
-// the table: d=3 M=189 (6 grid pairs) 3.66 -> 2.60 ms, d=2 M=2047 (7 pairs) 1.27 -> 1.20
-// ms, M=805 0.211 -> 0.202.  fp32 (segments of 256 bytes instead of 512 per
+// In the kernels above each lane gathers its own row, at a cache-line lookup per
+// lane and load: d=3 M=189 (6 grid pairs) 3.66 -> 2.60 ms, d=2 M=2047 (7 pairs) 1.27 ->
+// 1.20 ms, M=805 0.211 -> 0.202.  What bounds this one is not established.  In 3-D it
+// moves the mode values at 4.1 TB/s, near a copy's 4.7.  In 2-D 8.2 GB leave the L2s per
+// launch (6.8 TB/s, so part of it from the cache behind them): 3.8 of mode values and
+// 4.3 of table, which is every point's 8 lines of 128 bytes with no reuse.  fp32 (segments of 256 bytes instead of 512 per
 // pattern) loses: d=2 M=2047 0.350 -> 0.373, d=3 M=115 0.223 -> 0.260; and so do several
 // vector sets in 2-D, whose row mode_radial2_kernel keeps in registers: 16
 // sets M=805 2.45 -> 2.96.  Taking the mirrored point (n_1, n_0), which shares the row,

@@ -901,8 +901,8 @@ void fft_all(Plan* P, int sign) {
   // dimension 1 between B [G][na2][na1][mp] and B2 [G][na2][mc][mp], dimension 2
   // between B2 and C [G][mc][mc][mp].  Where mp rounds mc (odd) up to whole
   // 128-byte lines, a workgroup's 8 (fp64) or 16 (fp32) columns are one line of
-  // each row.  The passes move 51 GB per product at d=3 M=189 fp64 in 9.7 ms,
-  // 4.0 to 4.4 TB/s against 4.7 of a copy.
+  // each row.  The passes move 42 GB per product at d=3 M=189 fp64 in 9.6 ms,
+  // 4.1 to 4.7 TB/s against 4.7 of a copy.
   const int64_t mp = P->mp;
   FftPass x;
   x.L = nf; x.inner = 1; x.sign = sign;

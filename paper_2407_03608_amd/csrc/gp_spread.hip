@@ -5,8 +5,10 @@
 // with one wavefront per sub-tile and one cell per lane.  The points whose
 // window reaches a sub-tile are listed once per plan (in the order the sorted
 // points are visited), so a matvec streams exactly the contributing points of
-// each sub-tile, and the summation order of every cell is that list order (the
-// result is bitwise reproducible; no atomics, no zero-fill pass, plain stores).
+// each sub-tile.  Every cell is summed in a fixed order: the list four points at a
+// time, added by one matrix instruction in fp64, while fp32 keeps four sums, of every
+// fourth point each, that are joined at the end (the result is bitwise reproducible;
+// no atomics, no zero-fill pass, plain stores).
 #include <algorithm>
 #include <limits>
 
