@@ -378,6 +378,7 @@ def test_multi_split_lists_memory(gp, d, n, M, n_sigma, m, prec):
     Y = cuda(y)
     before = host(P.matvec(Y[0]))
     torch.cuda.synchronize()
+    _trim_pool()
     free = torch.cuda.mem_get_info()[0]
     X = host(P.cg_solve_multi(Y, tol=1e-14, max_iter=2)[0])
     torch.cuda.synchronize()
@@ -437,11 +438,16 @@ def test_byte_limit_admits_plans_without_lists(gp, d, n, M, tol, prec, dw, n_sig
         gp.Plan(*arg, max_device_bytes=least - 1, **kw)
 
 
+def _hip():
+    """The HIP runtime of this process."""
+    import ctypes
+    return ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+
+
 def _trim_pool():
     """Hands the memory that the runtime's pool keeps for reuse back to the device."""
     import ctypes
-    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
-    hip = ctypes.CDLL(path)
+    hip = _hip()
     pool = ctypes.c_void_p()
     assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), 0) == 0
     assert hip.hipMemPoolTrimTo(pool, ctypes.c_size_t(0)) == 0
@@ -451,6 +457,8 @@ def test_plan_where_lists_do_not_fit_the_device(gp):
     """A plan without a byte limit on a device whose free memory holds its form without
     spreading lists, but not the one with them: built, as it was before there were
     lists, with the values of the plan with lists."""
+    import ctypes
+
     import torch
     n = 6_000_000
     g = torch.Generator("cuda").manual_seed(1)
@@ -469,8 +477,16 @@ def test_plan_where_lists_do_not_fit_the_device(gp):
     _trim_pool()
     # what the runtime's pool still holds is not known, so the room shrinks in steps until
     # the form with lists (a few hundred MB more) does not fit any more
-    fill = [torch.empty(torch.cuda.mem_get_info()[0] - full - (full >> 2), dtype=torch.uint8, device="cuda")]
+    hip, fill = _hip(), []
+
+    def take(nbytes):
+        p = ctypes.c_void_p()
+        assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(nbytes)) == 0
+        fill.append(p)
+
     try:
+        torch.cuda.empty_cache()
+        take(torch.cuda.mem_get_info()[0] - full - (full >> 2))
         for _ in range(24):
             room = torch.cuda.mem_get_info()[0]
             P = gp.Plan(*arg, **kw)
@@ -479,15 +495,15 @@ def test_plan_where_lists_do_not_fit_the_device(gp):
                 break
             P.close()
             _trim_pool()
-            fill.append(torch.empty(96 << 20, dtype=torch.uint8, device="cuda"))
+            take(96 << 20)
         say(f"lists at most {full >> 20} MB, without {lean >> 20} MB counted; built without at {room >> 20} MB free")
         assert info["device_bytes"] == lean
         got = P.matvec(a)
         assert float((got - want).abs().max() / want.abs().max()) <= ORDER_FP64
         P.close()
     finally:
-        del fill
-        torch.cuda.empty_cache()
+        for p in fill:
+            assert hip.hipFree(p) == 0
 
 
 @pytest.mark.parametrize("d,n,m,prec", [(1, 300, 1, 0), (2, 3000, 5000, 0), (2, 900, 40, 1), (3, 500, 300, 0)])
