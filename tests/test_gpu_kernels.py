@@ -473,29 +473,28 @@ def test_plan_where_lists_do_not_fit_the_device(gp):
     want = P.matvec(a)
     P.close()
     lean = gp.plan_query(*arg, max_device_bytes=1, **kw)
-    torch.cuda.synchronize()
-    _trim_pool()
     # what the runtime's pool still holds is not known, so the room shrinks in steps until
     # the form with lists (a few hundred MB more) does not fit any more
     hip, fill = _hip(), []
 
-    def take(nbytes):
-        p = ctypes.c_void_p()
-        assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(nbytes)) == 0
-        fill.append(p)
+    def leave(room):
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        _trim_pool()
+        p, free = ctypes.c_void_p(), torch.cuda.mem_get_info()[0]
+        if free > room:
+            assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(free - room)) == 0
+            fill.append(p)
 
     try:
-        torch.cuda.empty_cache()
-        take(torch.cuda.mem_get_info()[0] - full - (full >> 2))
-        for _ in range(24):
-            room = torch.cuda.mem_get_info()[0]
+        for k in range(40):
+            room = full + (full >> 2) - k * (96 << 20)
+            leave(room)
             P = gp.Plan(*arg, **kw)
             info = P.info()
             if info["device_bytes"] == lean:
                 break
             P.close()
-            _trim_pool()
-            take(96 << 20)
         say(f"lists at most {full >> 20} MB, without {lean >> 20} MB counted; built without at {room >> 20} MB free")
         assert info["device_bytes"] == lean
         got = P.matvec(a)
